@@ -2,6 +2,7 @@
 
     python -m paper_1912_08063_amd.build      # or paper_1912_08063_amd.build.build()
 """
+import concurrent.futures
 import os
 import subprocess
 import sys
@@ -13,12 +14,23 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfwi.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["fwi_kernels.hip", "fwi_runtime.cpp", "revolve.cpp"]
+# (source, extra flags, object): the 3-D step kernels, most of the compile
+# time, build once per stencil radius, the largest first
+KERNELS = [("fwi_step3d.hip", ["-DFWI_STEP3D_M=%d" % m], "fwi_step3d_m%d.o" % m)
+           for m in (8, 4, 2, 1)] + [("fwi_step2d.hip", [], "fwi_step2d.o"),
+                                     ("fwi_kernels.hip", [], "fwi_common.o")]
+HOST = ["fwi_runtime.cpp", "revolve.cpp"]
 # packed-fp32 instructions are disabled: hand-written or generated
 # v_pk_{add,mul,fma}_f32 are avoided on this target.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
                 "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-I", INCLUDE, "-I", CSRC]
+
+
+def _run(cmd, verbose):
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
 
 
 def build(verbose=False, out=None, extra=None):
@@ -27,25 +39,23 @@ def build(verbose=False, out=None, extra=None):
     extra = list(extra or []) + os.environ.get("FWI_HIPCC_FLAGS", "").split()
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for src in SOURCES:
-        path = os.path.join(CSRC, src)
-        obj = os.path.join(objdir, src + ".o")
-        if src.endswith(".hip"):
-            cmd = [HIPCC] + COMMON + DEVICE_FLAGS + extra + ["-x", "hip", "-c", path, "-o", obj]
-        else:   # host-only C++ (HIP runtime API only)
-            cmd = [HIPCC] + COMMON + ["-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
-                                      "-c", path, "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
-        objs.append(obj)
+    obj = lambda name: os.path.join(objdir, name)
+    cmds = [[HIPCC] + COMMON + DEVICE_FLAGS + extra + flags +
+            ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj(o)]
+            for src, flags, o in KERNELS]
+    cmds += [[HIPCC] + COMMON +   # host-only C++ (HIP runtime API only)
+             ["-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-c",
+              os.path.join(CSRC, src), "-o", obj(src + ".o")] for src in HOST]
+    jobs = int(os.environ.get("MAX_JOBS", min(8, os.cpu_count() or 1)))
+    with concurrent.futures.ThreadPoolExecutor(max(1, jobs)) as pool:
+        list(pool.map(lambda c: _run(c, verbose), cmds))
+    # one object with every kernel, which other builds of the host code link
+    kernels = obj("fwi_kernels.hip.o")
+    _run(["ld", "-r", "-o", kernels] + [obj(o) for _, _, o in KERNELS], verbose)
     lib = out or LIB
     tmp = lib + ".tmp"
-    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    _run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, kernels] +
+         [obj(src + ".o") for src in HOST], verbose)
     os.replace(tmp, lib)
     return lib
 

@@ -31,1023 +31,12 @@
 //    level map places it in a snapshot field: binomial checkpointing then
 //    reads restored states and writes snapshot states in place, without
 //    copies.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
+#include <algorithm>
 #include <mutex>
 
-#include "fwi_internal.h"
+#include "fwi_device.h"
 
 namespace fwi {
-
-// ----------------------------------------------------------------- weights
-// Maximal-order central second-derivative weights:
-//   c_m = 2 (-1)^{m+1} (M!)^2 / (m^2 (M-m)! (M+m)!)   (difference form: c_0 unused)
-__host__ __device__ constexpr double factd(int n) { return n <= 1 ? 1.0 : double(n) * factd(n - 1); }
-__host__ __device__ constexpr double weightd(int M, int m)
-{
-    return 2.0 * ((m & 1) ? 1.0 : -1.0) * factd(M) * factd(M) /
-           (double(m) * double(m) * factd(M - m) * factd(M + m));
-}
-template <int M>
-struct Weights {
-    float c[M + 1];
-    float t3[M + 1], t2[M + 1];   // -6 resp. -4 times sum_{m > k} c_m
-    __host__ __device__ constexpr Weights() : c(), t3(), t2()
-    {
-        for (int m = 1; m <= M; ++m) c[m] = float(weightd(M, m));
-        for (int k = 0; k <= M; ++k) {
-            double t = 0.0;
-            for (int m = k + 1; m <= M; ++m) t += weightd(M, m);
-            t3[k] = float(-6.0 * t);
-            t2[k] = float(-4.0 * t);
-        }
-    }
-};
-
-// Radius 1, which carries most of the weight (c_1 = 1.6 of sum |c_m| = 1.83
-// at 8th order), is summed in difference form (p_{+1} - p) + (p_{-1} - p),
-// exact for neighbouring values of similar size.  The outer radii add plain
-// neighbour sums and one -2 D (sum_{m>1} c_m) p term: half the arithmetic,
-// and their rounding (about 6 eps |p| times their small weights) stays below
-// that of radius 1.  Measured against the FP64 oracle, every parity case
-// keeps its error within a factor of two of the all-difference form, and
-// the 16th-order step runs 19 % faster.  FWI_DIFF_RADII at build time sets
-// another number of difference-form radii (99: all).
-#ifndef FWI_DIFF_RADII
-#define FWI_DIFF_RADII 1
-#endif
-constexpr int kDiffRadii = FWI_DIFF_RADII;
-
-// ----------------------------------------------------------------- helpers
-__device__ __forceinline__ int sponge_depth(int i, int n, int nb)
-{
-    // cells into the sponge along one axis: max(nb - i, i - (n - 1 - nb), 0)
-    return max(max(nb - i, i - (n - 1 - nb)), 0);
-}
-
-__device__ __forceinline__ int find_job(const int *__restrict__ prefix, int njobs, int b)
-{
-    int lo = 0, hi = njobs;   // prefix[lo] <= b < prefix[hi]
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= b) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// Blocks are dealt round-robin to the 8 XCDs; give XCD k the k-th contiguous
-// eighth of the tile range instead (a bijection on [0, T)).
-__device__ __forceinline__ int xcd_remap(int b, int T)
-{
-    const int q = T >> 3, r = T & 7, k = b & 7, i = b >> 3;
-    return k * q + min(k, r) + i;
-}
-
-__device__ __forceinline__ int mod_pos(int a, int R) { int m = a % R; return m < 0 ? m + R : m; }
-
-// Time level a launch's step updates for job J: n0 + step (forward) or
-// k0 - step (adjoint), or, for jobs that change direction within a chunk
-// (binomial checkpointing in the serving path), the step's entry of the job's
-// level list (kNoLevel: no step of this launch's direction in that round).
-__device__ __forceinline__ int step_level(const Job *__restrict__ J, int step, bool adj)
-{
-    // The list entry is block-uniform, but the compiler cannot see that through
-    // a global load; without readfirstlane every plane base and buffer
-    // resource derived from it would be built lane by lane (waterfall loops,
-    // 20 % slower steps).
-    if (J->lev) return __builtin_amdgcn_readfirstlane(J->lev[step]);
-    return adj ? J->k0 - step : J->n0 + step;
-}
-
-// Field of forward level L: the ring slot L mod R, or a snapshot field the
-// level map names (block-uniform, scalar).
-__device__ __forceinline__ float *level_ptr(const Job *__restrict__ J, const LevelMap &lm, int L)
-{
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        if (lm.lev[i] == L) return J->snap + (int64_t)lm.fld[i] * J->fstride;
-    return J->ring + (int64_t)mod_pos(L, J->R) * J->fstride;
-}
-
-// Receiver sampling: traces[n-1][r] = p^n[rec_r] (level n is read-only here).
-__device__ __forceinline__ void gather_block(const Job *__restrict__ J, const LevelMap &lm, int r,
-                                             int n)
-{
-    if (!J->record || n < 1 || n > J->nt || r >= J->nrec) return;
-    const float *cur = level_ptr(J, lm, n);
-    J->traces[(int64_t)(n - 1) * J->nrec + r] = cur[J->rec_off[r]];
-}
-
-// Adjoint source at receiver r (the first of its cell): the sum of
-// res[k-1] over the receivers sharing the cell, in index order, so the
-// result is deterministic.  psi'^k gains kappa' times it (alpha = 1 on the
-// model grid, where every receiver sits).
-__device__ __forceinline__ float adj_source(const Job *__restrict__ J, int k, int r)
-{
-    const float *res = J->res + (int64_t)(k - 1) * J->nrec;
-    float s = res[r];
-    for (int q = J->rec_next[r]; q >= 0; q = J->rec_next[q]) s += res[q];
-    return s;
-}
-
-// Sponge factors from the squared depth d2 = sum_a d_a^2 into the sponge:
-// eta dt = eta_dt * d2, alpha = 1/(1 + eta dt), beta = (1 - eta dt) alpha.
-// out = alpha * val - beta * prev, written as alpha * (val - (1 - e) prev).
-__device__ __forceinline__ float leapfrog(float val, float prev, int d2, float eta_dt)
-{
-    if (d2 == 0) return val - prev;
-    const float e = eta_dt * (float)d2;
-    return __builtin_amdgcn_rcpf(1.f + e) * fmaf(-(1.f - e), prev, val);
-}
-
-// Streams read or written once per launch (kappa', the previous level, the
-// new level, the gradient accumulator) are non-temporal, leaving L2 to the
-// rows that neighbouring tiles share (+4 % on the 3-D forward step; keeping
-// kappa' or the new level cached instead, for reuse by the next step from the
-// Infinity Cache, measured no faster).  FWI_STREAM_CACHED at build time
-// restores ordinary accesses.
-// Field pointers come from the job table, so the compiler cannot see that
-// they address global memory; without the cast every access would be a
-// flat load (64-bit address arithmetic per access, and flat loads also hold
-// the LDS counter, so each LDS wait would wait for the prefetches too).
-#define GMEM __attribute__((address_space(1)))
-typedef GMEM float gfloat;
-
-__device__ __forceinline__ const gfloat *gptr(const float *p) { return (const gfloat *)p; }
-__device__ __forceinline__ gfloat *gptr(float *p) { return (gfloat *)p; }
-
-// Plane accesses go through a buffer resource (base and size of one plane in
-// scalar registers) and a 32-bit per-lane byte offset: no per-lane address
-// arithmetic, and an offset past the plane reads zero instead of faulting.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit buffer, CDNA
-constexpr int kCacheNT = 2;              // non-temporal cache policy
-
-__device__ __forceinline__ rsrc_t plane_rsrc(const gfloat *f, int zmem, int64_t plane,
-                                             int pbytes)
-{
-    const float *p = (const float *)(f + (int64_t)zmem * plane);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, pbytes, kRsrcWord3);
-}
-__device__ __forceinline__ float ldb(rsrc_t r, uint32_t boff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, 0));
-}
-__device__ __forceinline__ float ldb_stream(rsrc_t r, uint32_t boff)
-{
-#ifdef FWI_STREAM_CACHED
-    return ldb(r, boff);
-#else
-    return __builtin_bit_cast(float,
-                              __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, kCacheNT));
-#endif
-}
-__device__ __forceinline__ void stb_stream(rsrc_t r, uint32_t boff, float v)
-{
-#ifdef FWI_STREAM_CACHED
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)boff, 0, 0);
-#else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)boff, 0,
-                                          kCacheNT);
-#endif
-}
-
-// Plane of a field: element (z, row, col) is at base[(z + M) * plane + row_offset].
-// The plane base is uniform across the block (scalar registers); per-thread
-// offsets within a plane are 32-bit, so every load is base + 32-bit offset.
-__device__ __forceinline__ const gfloat *plane_ptr(const gfloat *f, int zmem, int64_t plane)
-{
-    return f + (int64_t)zmem * plane;
-}
-__device__ __forceinline__ gfloat *plane_ptr(gfloat *f, int zmem, int64_t plane)
-{
-    return f + (int64_t)zmem * plane;
-}
-
-// Compile-time loop: f(Int<I>{}) for I = B .. E-1, fully unrolled, so an
-// index derived from I can select a register.
-template <int V>
-struct Int {
-    static constexpr int value = V;
-};
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(Int<B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
-// Byte offset past every plane: a buffer store to it is dropped by the
-// hardware's range check, so masked lanes need no branch around a store.
-constexpr uint32_t kDropOffset = 0x7ffffff0u;
-
-// Block barrier for LDS traffic only.  __syncthreads() is a workgroup fence
-// over all memory, so each wave first waits for every global load it has in
-// flight; a step kernel's prefetches for the next plane would then have to
-// arrive within the current plane.  The step kernels share nothing through
-// global memory within a launch (a cell's previous level, output and
-// gradient are read and written by the thread that owns it), so ordering
-// the LDS staging is enough.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// --------------------------------------------------------------- 3-D step
-// One block: NW wavefronts of RY rows each, a 64 (x) x NW*RY (y) tile,
-// marching a chunk of z.  Per plane z: the LDS buffer (z & 1) holds plane z of the propagated field
-// with an M-cell halo; registers hold the z-queue (planes z-M .. z+M, in a
-// ring indexed by the unrolled phase k, so no register moves), kappa' and
-// the previous level.  While plane z is computed, plane z+1 is already being
-// loaded (the next queue front, kappa', previous level, halos), and written
-// to the other LDS buffer afterwards: one barrier per plane.
-//
-// Step modes: the forward step; the adjoint step with the imaging condition
-// fused in (two stencil fields); and the adjoint as two single-field passes,
-// the psi update alone and the imaging condition g += psi^{k+1} * L'p^k
-// alone, each with the forward step's memory pattern (see launch_3d).
-enum StepMode { kFwd = 0, kAdj = 1, kAdjPsi = 2, kImage = 3 };
-
-// Planes a step kernel loads ahead of the one it computes (queue front,
-// kappa', previous level).  Two planes ahead measured no faster on the
-// 304^3 forward: 86.7 against 85.1 us per step with 4 x 4 blocks (211
-// registers), 85.9 with 4 x 2.  No launch bound caps the registers: one
-// wave per SIMD more spills (4 x 4 forward at 3 waves: 98 against 85 us;
-// fused adjoint at 4 waves: 190 against 171 us).
-template <int M, int MODE>
-constexpr int kLookahead = 1;
-
-template <int M, int MODE, int NW, int RY>
-__global__ __launch_bounds__(64 * NW) void k_step3d(const Job *__restrict__ jobs,
-                                                const int *__restrict__ prefix, int njobs,
-                                                int step, int ttiles, int remap, LevelMap lm)
-{
-    constexpr int TX = kTileX, TY = RY * NW, NT = 64 * NW;
-    constexpr int LX = TX + 2 * M, LY = TY + 2 * M, Q = 2 * M + 1, LS = LY * LX;
-    constexpr int NYH = (2 * M * TX + NT - 1) / NT;   // y-halo cells per thread
-    constexpr int NXH = (TY * 2 * M + NT - 1) / NT;   // x-halo cells per thread
-    constexpr bool ADJ = MODE != kFwd;     // adjoint time order and tiling
-    constexpr bool FUSED = MODE == kAdj;   // second stencil field (p^k) and g
-    constexpr bool IMG = MODE == kImage;
-    // single-field modes up to 8th order: halos travel with the queue front
-    // (loaded at plane z+M, the same iteration in which the neighbouring tiles
-    // load those rows as their own front, so the second read is an L2 hit)
-    // and wait in a register ring.  At 16th order the ring would hold 5 x 17
-    // values per thread; without it the step runs at 4 instead of 2 waves per
-    // SIMD and 46 % faster (122 vs 178 us on a 304^3 grid), while at 8th order
-    // the ring wins (89 vs 94 us).
-    constexpr bool HQ = !FUSED && M <= 4;
-    constexpr Weights<M> W{};
-    constexpr int KD = kDiffRadii < M ? kDiffRadii : M;   // radii in difference form
-    __shared__ float sp[2 * LS];
-    __shared__ float sf[FUSED ? 2 * LS : 1];
-
-    const int tid = threadIdx.x;
-    int b = blockIdx.x;
-    if (b >= ttiles) {   // receiver-sampling blocks (forward launches only)
-        if constexpr (ADJ) return;
-        const int gb = b - ttiles;
-        const int j = find_job(prefix + njobs + 1, njobs, gb);
-        const Job *J = jobs + j;
-        gather_block(J, lm, (gb - prefix[njobs + 1 + j]) * blockDim.x + tid, step_level(J, step, false));
-        return;
-    }
-    if (remap) b = xcd_remap(b, ttiles);
-    const int j = find_job(prefix, njobs, b);
-    const Job *__restrict__ J = jobs + j;
-    const int n = step_level(J, step, ADJ);
-    if (ADJ ? (n < J->adj_lo || n >= J->adj_hi) : (n < J->fwd_lo || n >= J->fwd_hi)) return;
-
-    const int nz = J->nz, ny = J->ny, nx = J->nx, pitch = J->pitch, nb = J->nb;
-    const int64_t plane = J->plane, fstride = J->fstride;
-    const Job::Tiling &T = J->tile[ADJ ? 1 : 0];
-    int local = b - prefix[j];
-    int tx, ty, tz;
-    if (T.flags & kTileZFast) {
-        tz = local % T.nzc;
-        local /= T.nzc;
-        tx = local % T.ntx;
-        ty = local / T.ntx;
-    } else {
-        tx = local % T.ntx;
-        local /= T.ntx;
-        ty = local % T.nty;
-        tz = local / T.nty;
-    }
-    const int z0 = tz * T.zc, z1 = min(z0 + T.zc, nz);
-    // marching direction: plane i of the chunk (i = 0 .. npl-1) is zs + dir * i
-    const int dir = (T.flags & kTileZAlt) && (tz & 1) ? -1 : 1;
-    const int zs = dir > 0 ? z0 : z1 - 1, npl = z1 - z0;
-
-    // cur: the stencil field; prv and kap: the two pointwise streams; out.
-    // Imaging mode: cur = p^k, prv = psi^{k+1}, kap = out = g.
-    const gfloat *cur, *prv, *kap = gptr(J->kappa);
-    gfloat *out;
-    const gfloat *fwd = nullptr;
-    gfloat *grad = nullptr;
-    const bool accum = ADJ && J->accumulate && n <= J->nt - 1;
-    if constexpr (IMG) {
-        if (!accum) return;
-        cur = gptr(level_ptr(J, lm, n));
-        prv = gptr(J->adj) + (int64_t)((n + 1) & 1) * fstride;
-        kap = gptr(J->grad);
-        out = gptr(J->grad);
-    } else if constexpr (ADJ) {
-        cur = gptr(J->adj) + (int64_t)((n + 1) & 1) * fstride;
-        prv = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        out = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        if constexpr (FUSED) {
-            fwd = gptr(level_ptr(J, lm, n));
-            grad = gptr(J->grad);
-        }
-    } else {
-        cur = gptr(level_ptr(J, lm, n));
-        prv = gptr(level_ptr(J, lm, n - 1));
-        out = gptr(level_ptr(J, lm, n + 1));
-    }
-    const float eta_dt = J->eta_dt;
-    const int pbytes = (int)(plane * (int64_t)sizeof(float));
-
-    // ---- per-thread geometry (loop invariant)
-    const int lane = tid & 63, wv = tid >> 6;
-    const int col = tx * TX + lane;   // memory column
-    const int x = col - M;            // padded-grid x
-    const bool ax = x >= 0 && x < nx;
-    // Loads are unconditional: a row past the frame is clamped to the last
-    // frame row and a column outside the row to its edge.  Both hold zeros
-    // (frames and row padding are zero-filled and never written), exactly
-    // the values a masked load would give, and no active cell reads them
-    // beyond that.  Stores stay masked.
-    const int last_row = ny + 2 * M - 1;   // memory rows per plane - 1
-    bool act[RY];
-    uint32_t roff[RY];   // byte offsets within a plane
-    uint32_t soff[RY];   // store offsets: kDropOffset for cells outside the grid
-    int dxy2[RY];
-    const int dxs = sponge_depth(x, nx, nb);
-#pragma unroll
-    for (int i = 0; i < RY; ++i) {
-        const int yy = ty * TY + wv * RY + i;
-        act[i] = ax && yy < ny;
-        roff[i] = 4u * (uint32_t)(min(yy + M, last_row) * pitch + col);
-        soff[i] = act[i] ? roff[i] : kDropOffset;
-        const int d = sponge_depth(yy, ny, nb);
-        dxy2[i] = d * d + dxs * dxs;
-    }
-    uint32_t hyo[NYH], hxo[NXH];
-    int hyl[NYH], hxl[NXH];
-#pragma unroll
-    for (int q = 0; q < NYH; ++q) {   // rows above and below the tile
-        const int h = tid + NT * q;
-        const int r = (h / TX) % (2 * M), c = h % TX;
-        const int ly = r < M ? r : r + TY;
-        const int yg = ty * TY - M + ly;
-        hyo[q] = 4u * (uint32_t)(min(yg + M, last_row) * pitch + tx * TX + c);
-        hyl[q] = h < 2 * M * TX ? ly * LX + M + c : -1;
-    }
-#pragma unroll
-    for (int q = 0; q < NXH; ++q) {   // columns left and right of the tile
-        const int h = tid + NT * q;
-        const int r = (h / (2 * M)) % TY, c = h % (2 * M);
-        const int lc = c < M ? c : c + TX;
-        const int cm = min(max(tx * TX - M + lc, 0), pitch - 1);
-        const int yg = ty * TY + r;
-        hxo[q] = 4u * (uint32_t)(min(yg + M, last_row) * pitch + cm);
-        hxl[q] = h < TY * 2 * M ? (M + r) * LX + lc : -1;
-    }
-    // source (forward): the block that owns it adds it at its plane
-    const bool src_blk = !ADJ && J->src_x >= tx * TX - M && J->src_x < tx * TX - M + TX &&
-                         J->src_y >= ty * TY && J->src_y < ty * TY + TY && J->src_z >= z0 &&
-                         J->src_z < z1;
-    float srcv = 0.f;
-    int src_row = -1;
-    if (src_blk && J->src_x == x) {
-        const int r = J->src_y - (ty * TY + wv * RY);
-        if (r >= 0 && r < RY) { src_row = r; srcv = J->src_scale * J->wavelet[n]; }
-    }
-
-    // ---- register queues.  Chunk plane j (j = -M .. npl-1+M, memory plane
-    // zs + dir j + M) lives in queue slot (j + M) % U.  While plane ii is
-    // computed from slots ii .. ii+2M (mod U), planes up to ii+M+D-1 are
-    // already loaded and the front plane ii+M+D is loaded straight into a
-    // free slot (U >= Q + D), so no register is copied after a load and the
-    // wave never waits for recent prefetches before it moves on.  kappa', the
-    // previous level (and g) of plane ii are in slot ii % (D + 1), loaded D
-    // planes ahead.  The plane loop is unrolled by U, a multiple of D + 1,
-    // so every slot index is a compile-time constant.  Halos staged from
-    // memory at the end of a plane (no halo ring) are loaded one plane ahead,
-    // first, so that the wait for them leaves the rest in flight.
-    constexpr int D = kLookahead<M, MODE>;
-    constexpr int P = D + 1;
-    constexpr int U = (Q + D + P - 1) / P * P;
-    float q[RY][U];
-    float f[FUSED ? RY : 1][FUSED ? U : 1];
-    float hy[HQ ? NYH : 1][HQ ? U : 1], hx[HQ ? NXH : 1][HQ ? U : 1];
-    if constexpr (HQ) {
-        // halos of chunk planes 1 .. M+D-1 (slots M+1 .. 2M+D-1)
-#pragma unroll
-        for (int s = M + 1; s < Q + D - 1; ++s) {
-            if (s - M >= npl) continue;
-            const rsrc_t ph = plane_rsrc(cur, zs + dir * (s - M) + M, plane, pbytes);
-#pragma unroll
-            for (int h = 0; h < NYH; ++h) hy[h][s] = ldb(ph, hyo[h]);
-#pragma unroll
-            for (int h = 0; h < NXH; ++h) hx[h][s] = ldb(ph, hxo[h]);
-        }
-    }
-    // chunk planes -M .. M+D-1 (plane j is first read by the stencil of
-    // plane j - M, so planes past the chunk's last plane + M are skipped)
-#pragma unroll
-    for (int s = 0; s < Q + D - 1; ++s) {
-        if (s >= Q && s - 2 * M >= npl) continue;
-        const int zm = zs + dir * (s - M) + M;
-        const rsrc_t pc = plane_rsrc(cur, zm, plane, pbytes);
-        const rsrc_t pf = plane_rsrc(fwd, zm, plane, pbytes);
-#pragma unroll
-        for (int i = 0; i < RY; ++i) {
-            q[i][s] = ldb(pc, roff[i]);
-            if constexpr (FUSED) f[i][s] = ldb(pf, roff[i]);
-        }
-    }
-    float kv[P][RY], pv[P][RY], gv[FUSED ? P : 1][FUSED ? RY : 1];
-    // pointwise streams of planes 1 .. D-1
-#pragma unroll
-    for (int a = 1; a < D; ++a) {
-        if (a >= npl) continue;
-        const rsrc_t pk = plane_rsrc(kap, zs + dir * a + M, plane, pbytes);
-        const rsrc_t pp = plane_rsrc(prv, zs + dir * a + M, plane, pbytes);
-#pragma unroll
-        for (int i = 0; i < RY; ++i) {
-            kv[a][i] = ldb_stream(pk, roff[i]);
-            pv[a][i] = ldb_stream(pp, roff[i]);
-            if constexpr (FUSED)
-                gv[a][i] = accum ? ldb_stream(plane_rsrc(grad, zs + dir * a + M, plane, pbytes), roff[i])
-                                 : 0.f;
-        }
-    }
-    {
-        const rsrc_t pk = plane_rsrc(kap, zs + M, plane, pbytes);
-        const rsrc_t pp = plane_rsrc(prv, zs + M, plane, pbytes);
-#pragma unroll
-        for (int i = 0; i < RY; ++i) {
-            kv[0][i] = ldb(pk, roff[i]);
-            pv[0][i] = ldb(pp, roff[i]);
-            if constexpr (FUSED)
-                gv[0][i] = accum ? ldb(plane_rsrc(grad, zs + M, plane, pbytes), roff[i]) : 0.f;
-        }
-        const rsrc_t pc = plane_rsrc(cur, zs + M, plane, pbytes);
-        const rsrc_t pf = plane_rsrc(fwd, zs + M, plane, pbytes);
-        float *L = sp;           // LDS buffer i & 1 holds chunk plane i
-        float *LF = FUSED ? sf : nullptr;
-#pragma unroll
-        for (int i = 0; i < RY; ++i) {
-            L[(M + wv * RY + i) * LX + M + lane] = q[i][M];
-            if constexpr (FUSED) LF[(M + wv * RY + i) * LX + M + lane] = f[i][M];
-        }
-#pragma unroll
-        for (int h = 0; h < NYH; ++h)
-            if (hyl[h] >= 0) {
-                L[hyl[h]] = ldb(pc, hyo[h]);
-                if constexpr (FUSED) LF[hyl[h]] = ldb(pf, hyo[h]);
-            }
-#pragma unroll
-        for (int h = 0; h < NXH; ++h)
-            if (hxl[h] >= 0) {
-                L[hxl[h]] = ldb(pc, hxo[h]);
-                if constexpr (FUSED) LF[hxl[h]] = ldb(pf, hxo[h]);
-            }
-    }
-    lds_barrier();
-
-    // Plane ii of the chunk; k = ii % U selects the slots.  The main loop
-    // runs whole groups of U planes that all have a next plane (more), with
-    // no branch around a load or store, so the compiler's wait counts stay
-    // exact and only LDS waits remain at the barrier; the last group runs
-    // with those checks.
-    auto step_plane = [&](auto K, const int ii, const bool more, const bool ahead)
-        __attribute__((always_inline)) {
-            constexpr int k = decltype(K)::value;
-            const int z = zs + dir * ii;   // grid plane computed now
-            const int c = k % P, cn = (k + D) % P;   // pointwise slots of planes ii, ii+D
-            const int fs = (k + Q - 1 + D) % U;      // free queue slot: chunk plane ii+M+D
-            // ---- prefetch: halos of plane z+dir staged at the end of this
-            // plane (without a halo ring), then the queue front z+dir(1+M)
-            // and the pointwise streams of plane z+dir; memory plane = grid
-            // plane + M
-            float nhy[HQ ? 1 : NYH], nhx[HQ ? 1 : NXH];
-            float nfy[FUSED ? NYH : 1], nfx[FUSED ? NXH : 1];
-            const int zf = z + dir * (D + M) + M, zn = z + dir + M, za = z + dir * D + M;
-            if (more) {
-                if constexpr (!HQ) {
-                    const rsrc_t ph = plane_rsrc(cur, zn, plane, pbytes);
-#pragma unroll
-                    for (int h = 0; h < NYH; ++h) nhy[h] = ldb(ph, hyo[h]);
-#pragma unroll
-                    for (int h = 0; h < NXH; ++h) nhx[h] = ldb(ph, hxo[h]);
-                }
-                if constexpr (FUSED) {
-                    const rsrc_t fh = plane_rsrc(fwd, zn, plane, pbytes);
-#pragma unroll
-                    for (int h = 0; h < NYH; ++h) nfy[h] = ldb(fh, hyo[h]);
-#pragma unroll
-                    for (int h = 0; h < NXH; ++h) nfx[h] = ldb(fh, hxo[h]);
-                }
-            }
-            if (ahead) {
-                const rsrc_t pq = plane_rsrc(cur, zf, plane, pbytes);
-                const rsrc_t pk = plane_rsrc(kap, za, plane, pbytes);
-                const rsrc_t pp = plane_rsrc(prv, za, plane, pbytes);
-#pragma unroll
-                for (int i = 0; i < RY; ++i) {
-                    q[i][fs] = ldb(pq, roff[i]);
-                    kv[cn][i] = ldb_stream(pk, roff[i]);
-                    pv[cn][i] = ldb_stream(pp, roff[i]);
-                }
-                if constexpr (HQ) {
-#pragma unroll
-                    for (int h = 0; h < NYH; ++h) hy[h][fs] = ldb(pq, hyo[h]);
-#pragma unroll
-                    for (int h = 0; h < NXH; ++h) hx[h][fs] = ldb(pq, hxo[h]);
-                }
-                if constexpr (FUSED) {
-                    const rsrc_t fq = plane_rsrc(fwd, zf, plane, pbytes);
-                    const rsrc_t pg = plane_rsrc(grad, za, plane, pbytes);
-#pragma unroll
-                    for (int i = 0; i < RY; ++i) {
-                        f[i][fs] = ldb(fq, roff[i]);
-                        gv[cn][i] = accum ? ldb_stream(pg, roff[i]) : 0.f;
-                    }
-                }
-            }
-            // ---- plane z (queue slot (k + M + m) % U holds plane z + dir m)
-            const float *L = sp + (ii & 1) * LS;
-            const float *LF = FUSED ? sf + (ii & 1) * LS : nullptr;
-            const rsrc_t po = plane_rsrc(out, z + M, plane, pbytes);
-            const rsrc_t pg = plane_rsrc(grad, z + M, plane, pbytes);
-            const int dz = sponge_depth(z, nz, nb);
-            float res[RY];
-#pragma unroll
-            for (int i = 0; i < RY; ++i) {
-                const int ly = M + wv * RY + i, lx = M + lane;
-                const float pc = q[i][(k + M) % U];
-                float acc = 0.f;
-#pragma unroll
-                for (int m = M; m > KD; --m) {
-                    const float t = (L[ly * LX + lx + m] + L[ly * LX + lx - m]) +
-                                    (L[(ly + m) * LX + lx] + L[(ly - m) * LX + lx]) +
-                                    (q[i][(k + M + m) % U] + q[i][(k + M - m) % U]);
-                    acc = fmaf(W.c[m], t, acc);
-                }
-                if constexpr (KD < M) acc = fmaf(W.t3[KD], pc, acc);
-#pragma unroll
-                for (int m = KD; m >= 1; --m) {
-                    const float d = ((L[ly * LX + lx + m] - pc) + (L[ly * LX + lx - m] - pc)) +
-                                    ((L[(ly + m) * LX + lx] - pc) + (L[(ly - m) * LX + lx] - pc)) +
-                                    ((q[i][(k + M + m) % U] - pc) + (q[i][(k + M - m) % U] - pc));
-                    acc = fmaf(W.c[m], d, acc);
-                }
-                // imaging: g + psi^{k+1} * L'p^k (kv holds g, pv psi^{k+1}),
-                // the same operation as the fused kernel's
-                res[i] = IMG ? fmaf(pv[c][i], acc, kv[c][i]) : fmaf(kv[c][i], acc, 2.f * pc);
-            }
-            if (src_blk && z == J->src_z) {
-#pragma unroll
-                for (int i = 0; i < RY; ++i) res[i] += i == src_row ? srcv : 0.f;
-            }
-#pragma unroll
-            for (int i = 0; i < RY; ++i) {
-                if constexpr (IMG)
-                    stb_stream(po, soff[i], res[i]);
-                else
-                    stb_stream(po, soff[i], leapfrog(res[i], pv[c][i], dxy2[i] + dz * dz, eta_dt));
-            }
-            if constexpr (FUSED) {
-                if (accum) {
-#pragma unroll
-                    for (int i = 0; i < RY; ++i) {
-                        const int ly = M + wv * RY + i, lx = M + lane;
-                        const float fc = f[i][(k + M) % U];
-                        float lf = 0.f;
-#pragma unroll
-                        for (int m = M; m > KD; --m) {
-                            const float t = (LF[ly * LX + lx + m] + LF[ly * LX + lx - m]) +
-                                            (LF[(ly + m) * LX + lx] + LF[(ly - m) * LX + lx]) +
-                                            (f[i][(k + M + m) % U] + f[i][(k + M - m) % U]);
-                            lf = fmaf(W.c[m], t, lf);
-                        }
-                        if constexpr (KD < M) lf = fmaf(W.t3[KD], fc, lf);
-#pragma unroll
-                        for (int m = KD; m >= 1; --m) {
-                            const float d =
-                                ((LF[ly * LX + lx + m] - fc) + (LF[ly * LX + lx - m] - fc)) +
-                                ((LF[(ly + m) * LX + lx] - fc) + (LF[(ly - m) * LX + lx] - fc)) +
-                                ((f[i][(k + M + m) % U] - fc) + (f[i][(k + M - m) % U] - fc));
-                            lf = fmaf(W.c[m], d, lf);
-                        }
-                        stb_stream(pg, soff[i], fmaf(q[i][(k + M) % U], lf, gv[c][i]));
-                    }
-                }
-            }
-            // ---- stage plane z+dir in the other LDS buffer
-            if (more) {
-                float *Ln = sp + ((ii + 1) & 1) * LS;
-                float *LFn = FUSED ? sf + ((ii + 1) & 1) * LS : nullptr;
-#pragma unroll
-                for (int i = 0; i < RY; ++i) {
-                    Ln[(M + wv * RY + i) * LX + M + lane] = q[i][(k + M + 1) % U];
-                    if constexpr (FUSED)
-                        LFn[(M + wv * RY + i) * LX + M + lane] = f[i][(k + M + 1) % U];
-                }
-#pragma unroll
-                for (int h = 0; h < NYH; ++h)
-                    if (hyl[h] >= 0) {
-                        if constexpr (HQ) Ln[hyl[h]] = hy[h][(k + M + 1) % U];
-                        else Ln[hyl[h]] = nhy[h];
-                        if constexpr (FUSED) LFn[hyl[h]] = nfy[h];
-                    }
-#pragma unroll
-                for (int h = 0; h < NXH; ++h)
-                    if (hxl[h] >= 0) {
-                        if constexpr (HQ) Ln[hxl[h]] = hx[h][(k + M + 1) % U];
-                        else Ln[hxl[h]] = nhx[h];
-                        if constexpr (FUSED) LFn[hxl[h]] = nfx[h];
-                    }
-            }
-            lds_barrier();
-    };
-    int ib = 0;
-    for (; ib + U - 1 + D < npl; ib += U)
-        static_for<0, U>([&](auto K) __attribute__((always_inline)) {
-            step_plane(K, ib + decltype(K)::value, true, true);
-        });
-    static_for<0, U>([&](auto K) __attribute__((always_inline)) {
-        const int ii = ib + decltype(K)::value;
-        if (ii < npl) step_plane(K, ii, ii + 1 < npl, ii + D < npl);
-    });
-}
-
-// --------------------------------------------------------------- 2-D step
-// One wavefront per block: 64 columns marching down a chunk of rows with a
-// (2M+1)-row register queue; the current row with its halo is staged in a
-// double-buffered LDS row, and row z+1 is loaded while row z is computed.
-template <int M, bool ADJ>
-__global__ __launch_bounds__(64) void k_step2d(const Job *__restrict__ jobs,
-                                               const int *__restrict__ prefix, int njobs,
-                                               int step, int ttiles, int remap, LevelMap lm)
-{
-    constexpr int TX = kTileX, LX = TX + 2 * M, Q = 2 * M + 1;
-    constexpr Weights<M> W{};
-    constexpr int KD = kDiffRadii < M ? kDiffRadii : M;   // radii in difference form
-    __shared__ float sp[2 * LX];
-    __shared__ float sf[ADJ ? 2 * LX : 1];
-    __shared__ float sinj[ADJ ? TX : 1];   // adjoint source of the current row
-
-    const int lane = threadIdx.x;
-    int b = blockIdx.x;
-    if (b >= ttiles) {
-        if constexpr (ADJ) return;
-        const int gb = b - ttiles;
-        const int j = find_job(prefix + njobs + 1, njobs, gb);
-        const Job *J = jobs + j;
-        gather_block(J, lm, (gb - prefix[njobs + 1 + j]) * blockDim.x + lane, step_level(J, step, false));
-        return;
-    }
-    if (remap) b = xcd_remap(b, ttiles);
-    const int j = find_job(prefix, njobs, b);
-    const Job *__restrict__ J = jobs + j;
-    const int n = step_level(J, step, ADJ);
-    if (ADJ ? (n < J->adj_lo || n >= J->adj_hi) : (n < J->fwd_lo || n >= J->fwd_hi)) return;
-
-    const int nz = J->nz, nx = J->nx, pitch = J->pitch, nb = J->nb;
-    const int64_t fstride = J->fstride;
-    const Job::Tiling &T = J->tile[ADJ ? 1 : 0];
-    const int local = b - prefix[j];
-    const int tx = local % T.ntx;
-    const int tz = local / T.ntx;
-    const int z0 = tz * T.zc, z1 = min(z0 + T.zc, nz);
-    // adjoint: the psi update adds the adjoint source at this tile's receiver
-    // cells (a list sorted by row; at most one cell per column)
-    int rp = 0, re = 0;
-    if constexpr (ADJ) {
-        rp = J->rt_start[local];
-        re = J->rt_start[local + 1];
-    }
-
-    const gfloat *cur, *prv;
-    gfloat *out;
-    const gfloat *fwd = nullptr;
-    gfloat *grad = nullptr;
-    bool accum = false;
-    if constexpr (ADJ) {
-        cur = gptr(J->adj) + (int64_t)((n + 1) & 1) * fstride;
-        prv = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        out = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        accum = J->accumulate && n <= J->nt - 1;
-        fwd = gptr(level_ptr(J, lm, n));
-        grad = gptr(J->grad);
-    } else {
-        cur = gptr(level_ptr(J, lm, n));
-        prv = gptr(level_ptr(J, lm, n - 1));
-        out = gptr(level_ptr(J, lm, n + 1));
-    }
-    const gfloat *kap = gptr(J->kappa);
-    const float eta_dt = J->eta_dt;
-
-    const int col = tx * TX + lane;
-    const int x = col - M;
-    const bool act = x >= 0 && x < nx;
-    const int dxs = sponge_depth(x, nx, nb);
-    // halo lanes: lane < 2M loads column tx*TX - M + (lane < M ? lane : lane + TX)
-    const int hl = lane < M ? lane : lane + TX;
-    const int hcol = tx * TX - M + hl;
-    const bool hact = lane < 2 * M && hcol >= 0 && hcol < pitch;
-    const int hcl = min(max(hcol, 0), pitch - 1);   // a column inside the row
-    const bool src_here = !ADJ && J->src_x == x && J->src_z >= z0 && J->src_z < z1;
-    const float srcv = src_here ? J->src_scale * J->wavelet[n] : 0.f;
-    const int64_t p64 = pitch;
-
-    // Register queue of U = Q + 1 rows: chunk row j (row z0 + j, j = -M ..)
-    // in slot (j + M) % U; the front row is loaded straight into the free
-    // slot and kappa', the previous level (and g) alternate between two
-    // slots, so no freshly loaded register is copied and the wave keeps the
-    // next row's loads in flight while it computes (as in the 3-D kernel).
-    // Lanes outside the grid load and store zeros in the row's frame and
-    // padding, which hold zeros, so stores need no mask.
-    constexpr int U = Q + 1;
-    float q[U];
-    float f[ADJ ? U : 1];
-#pragma unroll
-    for (int s = 0; s < Q; ++s) {   // rows z0 - M .. z0 + M
-        q[s] = act ? cur[(int64_t)(z0 + s) * p64 + col] : 0.f;
-        if constexpr (ADJ) f[s] = act ? fwd[(int64_t)(z0 + s) * p64 + col] : 0.f;
-    }
-    float kv[2], pv[2], gv[2];
-    kv[0] = act ? kap[(int64_t)(z0 + M) * p64 + col] : 0.f;
-    pv[0] = act ? prv[(int64_t)(z0 + M) * p64 + col] : 0.f;
-    gv[0] = 0.f;
-    if constexpr (ADJ) gv[0] = act && accum ? grad[(int64_t)(z0 + M) * p64 + col] : 0.f;
-    {
-        float *L = sp + (z0 & 1) * LX;
-        L[M + lane] = q[M];
-        if (lane < 2 * M) L[hl] = hact ? cur[(int64_t)(z0 + M) * p64 + hcol] : 0.f;
-        if constexpr (ADJ) {
-            float *LF = sf + (z0 & 1) * LX;
-            LF[M + lane] = f[M];
-            if (lane < 2 * M) LF[hl] = hact ? fwd[(int64_t)(z0 + M) * p64 + hcol] : 0.f;
-        }
-    }
-    lds_barrier();
-
-    // row z = z0 + ii; k = ii % U selects the slots
-    auto step_row = [&](auto K, const int z, const bool more) __attribute__((always_inline)) {
-            constexpr int k = decltype(K)::value;
-            const int c = k & 1, cn = c ^ 1;   // pointwise slots of rows z, z+1
-            const int fs = (k + U - 1) % U;    // free queue slot: row z+M+1
-            // halos of row z+1 (staged at the end of this row) first.  The
-            // loads are not predicated (a skipped load would make the wait
-            // counts after it inexact): lanes outside the grid read the zero
-            // frame and padding of their row, halo lanes a clamped column.
-            float nh = 0.f, nfh = 0.f;
-            if (more) {
-                const int64_t rf = (int64_t)(z + 1 + 2 * M) * p64, rc = (int64_t)(z + 1 + M) * p64;
-                const float h = cur[rc + hcl];
-                nh = hact ? h : 0.f;
-                if constexpr (ADJ) {
-                    const float hf = fwd[rc + hcl];
-                    nfh = hact ? hf : 0.f;
-                }
-                q[fs] = cur[rf + col];
-                kv[cn] = kap[rc + col];
-                pv[cn] = prv[rc + col];
-                if constexpr (ADJ) {
-                    f[fs] = fwd[rf + col];
-                    const float g = grad[rc + col];
-                    gv[cn] = accum ? g : 0.f;
-                }
-            }
-            const float *L = sp + (z & 1) * LX;
-            const int lx = M + lane;
-            const float pc = q[(k + M) % U];
-            float acc = 0.f;
-#pragma unroll
-            for (int m = M; m > KD; --m) {
-                const float t = (L[lx + m] + L[lx - m]) + (q[(k + M + m) % U] + q[(k + M - m) % U]);
-                acc = fmaf(W.c[m], t, acc);
-            }
-            if constexpr (KD < M) acc = fmaf(W.t2[KD], pc, acc);
-#pragma unroll
-            for (int m = KD; m >= 1; --m) {
-                const float d = ((L[lx + m] - pc) + (L[lx - m] - pc)) +
-                                ((q[(k + M + m) % U] - pc) + (q[(k + M - m) % U] - pc));
-                acc = fmaf(W.c[m], d, acc);
-            }
-            float val = fmaf(kv[c], acc, 2.f * pc);
-            if (src_here && z == J->src_z) val += srcv;
-            const int dz = sponge_depth(z, nz, nb);
-            const int64_t rz = (int64_t)(z + M) * p64 + col;
-            float o = leapfrog(val, pv[c], dxs * dxs + dz * dz, eta_dt);
-            if constexpr (ADJ) {
-                // receivers on row z: lane i takes the list's i-th, and the sum
-                // reaches the lane of its column through LDS
-                if (rp < re && (J->rt_key[rp] >> 6) == z) {
-                    const int idx = rp + lane;
-                    const int key = idx < re ? J->rt_key[idx] : -1;
-                    const int r = key >= 0 && (key >> 6) == z ? J->rt_rec[idx] : -1;
-                    sinj[lane] = 0.f;
-                    lds_barrier();
-                    if (r >= 0) sinj[key & 63] = adj_source(J, n, r);
-                    lds_barrier();
-                    if (act) o += kv[c] * sinj[lane];
-                    rp += __popcll(__ballot(r >= 0));
-                    lds_barrier();
-                }
-            }
-            out[rz] = o;   // zero outside the grid
-            if constexpr (ADJ) {
-                if (accum) {
-                    const float *LF = sf + (z & 1) * LX;
-                    const float fc = f[(k + M) % U];
-                    float lf = 0.f;
-#pragma unroll
-                    for (int m = M; m > KD; --m) {
-                        const float t = (LF[lx + m] + LF[lx - m]) + (f[(k + M + m) % U] + f[(k + M - m) % U]);
-                        lf = fmaf(W.c[m], t, lf);
-                    }
-                    if constexpr (KD < M) lf = fmaf(W.t2[KD], fc, lf);
-#pragma unroll
-                    for (int m = KD; m >= 1; --m) {
-                        const float d = ((LF[lx + m] - fc) + (LF[lx - m] - fc)) +
-                                        ((f[(k + M + m) % U] - fc) + (f[(k + M - m) % U] - fc));
-                        lf = fmaf(W.c[m], d, lf);
-                    }
-                    grad[rz] = fmaf(pc, lf, gv[c]);   // zero outside the grid
-                }
-            }
-            if (more) {
-                float *Ln = sp + ((z + 1) & 1) * LX;
-                Ln[M + lane] = q[(k + M + 1) % U];
-                if (lane < 2 * M) Ln[hl] = nh;
-                if constexpr (ADJ) {
-                    float *LFn = sf + ((z + 1) & 1) * LX;
-                    LFn[M + lane] = f[(k + M + 1) % U];
-                    if (lane < 2 * M) LFn[hl] = nfh;
-                }
-            }
-            lds_barrier();
-    };
-    int zb = z0;
-    for (; zb + U < z1; zb += U)
-        static_for<0, U>([&](auto K) __attribute__((always_inline)) {
-            step_row(K, zb + decltype(K)::value, true);
-        });
-    static_for<0, U>([&](auto K) __attribute__((always_inline)) {
-        const int z = zb + decltype(K)::value;
-        if (z < z1) step_row(K, z, z + 1 < z1);
-    });
-}
-
-// 2-D step for grids too small to fill the GPU: one block per tile row of 64
-// columns and one cell per lane, every neighbour loaded straight from memory
-// (the fields are cache-resident at these sizes).  Nothing is marched, so a
-// launch costs one round of load latency instead of the 2M + 1 row warm-up
-// and serial row loop of k_step2d.  The arithmetic is k_step2d's, term by term
-// in the same order, so both kernels give bitwise the same fields.  Tiles are
-// one row tall (Tiling.zc == 1); the adjoint takes this row's receiver cells
-// from the tile's list, as k_step2d does row by row.
-template <int M, bool ADJ>
-__global__ __launch_bounds__(64) void k_step2d_direct(const Job *__restrict__ jobs,
-                                                      const int *__restrict__ prefix, int njobs,
-                                                      int step, int ttiles, int remap,
-                                                      LevelMap lm)
-{
-    constexpr int TX = kTileX;
-    constexpr Weights<M> W{};
-    constexpr int KD = kDiffRadii < M ? kDiffRadii : M;   // radii in difference form
-    __shared__ float sinj[ADJ ? TX : 1];   // adjoint source of this row
-
-    const int lane = threadIdx.x;
-    int b = blockIdx.x;
-    if (b >= ttiles) {
-        if constexpr (ADJ) return;
-        const int gb = b - ttiles;
-        const int j = find_job(prefix + njobs + 1, njobs, gb);
-        const Job *J = jobs + j;
-        gather_block(J, lm, (gb - prefix[njobs + 1 + j]) * blockDim.x + lane, step_level(J, step, false));
-        return;
-    }
-    if (remap) b = xcd_remap(b, ttiles);
-    const int j = find_job(prefix, njobs, b);
-    const Job *__restrict__ J = jobs + j;
-    const int n = step_level(J, step, ADJ);
-    if (ADJ ? (n < J->adj_lo || n >= J->adj_hi) : (n < J->fwd_lo || n >= J->fwd_hi)) return;
-
-    const int nz = J->nz, nx = J->nx, pitch = J->pitch, nb = J->nb;
-    const int64_t fstride = J->fstride;
-    const Job::Tiling &T = J->tile[ADJ ? 1 : 0];
-    const int local = b - prefix[j];
-    const int tx = local % T.ntx;
-    const int z = local / T.ntx;   // one row per tile
-    if (z >= nz) return;
-
-    const gfloat *cur, *prv;
-    gfloat *out;
-    const gfloat *fwd = nullptr;
-    gfloat *grad = nullptr;
-    bool accum = false;
-    if constexpr (ADJ) {
-        cur = gptr(J->adj) + (int64_t)((n + 1) & 1) * fstride;
-        prv = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        out = gptr(J->adj) + (int64_t)(n & 1) * fstride;
-        accum = J->accumulate && n <= J->nt - 1;
-        fwd = gptr(level_ptr(J, lm, n));
-        grad = gptr(J->grad);
-    } else {
-        cur = gptr(level_ptr(J, lm, n));
-        prv = gptr(level_ptr(J, lm, n - 1));
-        out = gptr(level_ptr(J, lm, n + 1));
-    }
-    const gfloat *kap = gptr(J->kappa);
-    const float eta_dt = J->eta_dt;
-
-    const int col = tx * TX + lane;
-    const int x = col - M;
-    const bool act = x >= 0 && x < nx;
-    // every neighbour of an active cell lies inside the frame (zeros beyond the
-    // padded grid), where k_step2d reads the same values from LDS and its queue
-    const int64_t p64 = pitch, rz = (int64_t)(z + M) * p64 + col;
-    float o = 0.f, pc = 0.f, kv = 0.f, gv = 0.f, lf = 0.f;
-    if (act) {
-        pc = cur[rz];
-        kv = kap[rz];
-        const float pv = prv[rz];
-        float acc = 0.f;
-#pragma unroll
-        for (int m = M; m > KD; --m) {
-            const float t = (cur[rz + m] + cur[rz - m]) + (cur[rz + m * p64] + cur[rz - m * p64]);
-            acc = fmaf(W.c[m], t, acc);
-        }
-        if constexpr (KD < M) acc = fmaf(W.t2[KD], pc, acc);
-#pragma unroll
-        for (int m = KD; m >= 1; --m) {
-            const float d = ((cur[rz + m] - pc) + (cur[rz - m] - pc)) +
-                            ((cur[rz + m * p64] - pc) + (cur[rz - m * p64] - pc));
-            acc = fmaf(W.c[m], d, acc);
-        }
-        float val = fmaf(kv, acc, 2.f * pc);
-        // the source term rounded as in k_step2d: its product first, then the
-        // sum (never fused into one fma)
-        if (!ADJ && J->src_x == x && J->src_z == z) {
-#pragma clang fp contract(off)
-            const float srcv = J->src_scale * J->wavelet[n];
-            val = val + srcv;
-        }
-        const int dxs = sponge_depth(x, nx, nb), dz = sponge_depth(z, nz, nb);
-        o = leapfrog(val, pv, dxs * dxs + dz * dz, eta_dt);
-        if constexpr (ADJ) {
-            if (accum) {
-                gv = grad[rz];
-                const float fc = fwd[rz];
-#pragma unroll
-                for (int m = M; m > KD; --m) {
-                    const float t = (fwd[rz + m] + fwd[rz - m]) + (fwd[rz + m * p64] + fwd[rz - m * p64]);
-                    lf = fmaf(W.c[m], t, lf);
-                }
-                if constexpr (KD < M) lf = fmaf(W.t2[KD], fc, lf);
-#pragma unroll
-                for (int m = KD; m >= 1; --m) {
-                    const float d = ((fwd[rz + m] - fc) + (fwd[rz - m] - fc)) +
-                                    ((fwd[rz + m * p64] - fc) + (fwd[rz - m * p64] - fc));
-                    lf = fmaf(W.c[m], d, lf);
-                }
-            }
-        }
-    }
-    if constexpr (ADJ) {
-        // receivers on this row: lane i takes the list's i-th, and the sum
-        // reaches the lane of its column through LDS (block-uniform branch)
-        const int rp = J->rt_start[local], re = J->rt_start[local + 1];
-        if (rp < re) {
-            const int idx = rp + lane;
-            const int key = idx < re ? J->rt_key[idx] : -1;
-            const int r = key >= 0 ? J->rt_rec[idx] : -1;
-            sinj[lane] = 0.f;
-            __syncthreads();
-            if (r >= 0) sinj[key & 63] = adj_source(J, n, r);
-            __syncthreads();
-            o += kv * sinj[lane];
-        }
-    }
-    if (act) {
-        out[rz] = o;
-        if constexpr (ADJ) {
-            if (accum) grad[rz] = fmaf(pc, lf, gv);
-        }
-    }
-}
 
 // ------------------------------------------------------------ side kernels
 // kappa' = (v dt/dx)^2 on the padded grid (edge-replicated model), 0 on the frame.
@@ -1105,153 +94,6 @@ __global__ void k_snapshot(const Job *__restrict__ jobs, int slot, int time, int
         else r[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
-
-// Several forward steps of a small 2-D grid in one launch (temporal blocking
-// for launch-bound grids).  A block loads a region of p^n, p^{n-1} and kappa'
-// into LDS that extends the output tile by A = K M cells on every side, then
-// advances it kk <= K steps in LDS, each step on a region M cells narrower
-// (the apron cells are computed redundantly by neighbouring blocks), and
-// stores levels n+kk and n+kk-1 of its output tile.  Cells outside the padded
-// grid hold zero and are never updated, as the frame in memory.  Each cell's
-// arithmetic is k_step2d_direct's, term by term, so the fields and traces are
-// bitwise those of kk single steps.  The launch reads ring slots n, n-1 and
-// writes slots n+kk, n+kk-1, which must differ (ring length >= K + 2): no
-// block reads what another writes.  Traces of levels n .. n+kk are written by
-// the block whose output tile holds the receiver (level n too: a preceding
-// single step does not sample the level it produces).
-template <int M, int K>
-struct Multi2d {
-    static constexpr int A = K * M;                     // apron
-    static constexpr int RW = 64;                        // region width (one wave per row)
-    static constexpr int OX = RW - 2 * A, OZ = 16;       // output tile
-    static constexpr int RH = OZ + 2 * A, NR = RW * RH;  // region
-    static_assert(OX >= 16, "apron too wide for the region");
-};
-
-template <int M, int K>
-__global__ __launch_bounds__(1024) void k_step2d_multi(const Job *__restrict__ jobs,
-                                                       int tiles_per_job, int ntxm, int step,
-                                                       int kk, int record)
-{
-    using G = Multi2d<M, K>;
-    constexpr int A = G::A, RW = G::RW, OX = G::OX, OZ = G::OZ, RH = G::RH, NR = G::NR;
-    constexpr int NT = 1024, CPT = (NR + NT - 1) / NT;   // region cells per thread
-    constexpr int RPT = 2;                               // receivers resolved per thread
-    constexpr Weights<M> W{};
-    constexpr int KD = kDiffRadii < M ? kDiffRadii : M;
-    __shared__ float s0[NR], s1[NR], sk[NR];
-
-    const int tid = threadIdx.x;
-    const int j = blockIdx.x / tiles_per_job, t = blockIdx.x % tiles_per_job;
-    const Job *__restrict__ J = jobs + j;
-    const int n = step_level(J, step, false);
-    const int nz = J->nz, nx = J->nx, pitch = J->pitch, nb = J->nb, nrec = J->nrec;
-    const int x0 = (t % ntxm) * OX - A, z0 = (t / ntxm) * OZ - A;   // region origin
-    const gfloat *cur = gptr(level_ptr(J, LevelMap{}, n));
-    const gfloat *prv = gptr(level_ptr(J, LevelMap{}, n - 1));
-    const gfloat *kap = gptr(J->kappa);
-    gfloat *o1 = gptr(level_ptr(J, LevelMap{}, n + kk));
-    gfloat *o0 = gptr(level_ptr(J, LevelMap{}, n + kk - 1));
-    const float eta_dt = J->eta_dt;
-    const int64_t p64 = pitch;
-
-    // this thread's region cells: LDS index, grid coordinates, inside the grid
-    int ci[CPT], cx[CPT], cz[CPT];
-    bool cin[CPT];
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-        ci[q] = tid + q * NT;
-        cx[q] = x0 + ci[q] % RW;
-        cz[q] = z0 + ci[q] / RW;
-        cin[q] = ci[q] < NR && cx[q] >= 0 && cx[q] < nx && cz[q] >= 0 && cz[q] < nz;
-    }
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-        if (ci[q] >= NR) continue;
-        const int64_t off = (int64_t)(cz[q] + M) * p64 + (cx[q] + M);
-        s0[ci[q]] = cin[q] ? cur[off] : 0.f;
-        s1[ci[q]] = cin[q] ? prv[off] : 0.f;
-        sk[ci[q]] = cin[q] ? kap[off] : 0.f;
-    }
-    // receivers in this block's output tile: their LDS index (-1: elsewhere).
-    // Grids on this path are small, so field offsets fit 32 bits.
-    const bool rec_on = record && J->record;
-    auto local_of = [&](int r) {
-        const int off = (int)J->rec_off[r];
-        const int rx = off % pitch - M - x0, rz = off / pitch - M - z0;
-        return rx >= A && rx < A + OX && rz >= A && rz < A + OZ ? rz * RW + rx : -1;
-    };
-    int rl[RPT];
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-        const int r = tid + q * NT;
-        rl[q] = rec_on && r < nrec ? local_of(r) : -1;
-    }
-    // traces of level L (1 .. nt) from the LDS field f
-    auto sample = [&](const float *f, int L) {
-        if (!rec_on || L < 1 || L > J->nt) return;
-        float *tr = J->traces + (int64_t)(L - 1) * nrec;
-#pragma unroll
-        for (int q = 0; q < RPT; ++q)
-            if (rl[q] >= 0) tr[tid + q * NT] = f[rl[q]];
-        for (int r = tid + RPT * NT; r < nrec; r += NT) {
-            const int li = local_of(r);
-            if (li >= 0) tr[r] = f[li];
-        }
-    };
-    __syncthreads();
-    sample(s0, n);
-
-    float *cu = s0, *pr = s1;   // levels L and L-1; the step writes L+1 over L-1
-    for (int st = 0; st < kk; ++st) {
-        const int L = n + st, lo = (st + 1) * M;
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-            const int i = ci[q], rx = i % RW, rz = i / RW;
-            if (!cin[q] || rx < lo || rx >= RW - lo || rz < lo || rz >= RH - lo) continue;
-            const int x = cx[q], z = cz[q];
-            const float pc = cu[i];
-            const float kv = sk[i];
-            const float pv = pr[i];
-            float acc = 0.f;
-#pragma unroll
-            for (int m = M; m > KD; --m) {
-                const float tt = (cu[i + m] + cu[i - m]) + (cu[i + m * RW] + cu[i - m * RW]);
-                acc = fmaf(W.c[m], tt, acc);
-            }
-            if constexpr (KD < M) acc = fmaf(W.t2[KD], pc, acc);
-#pragma unroll
-            for (int m = KD; m >= 1; --m) {
-                const float d = ((cu[i + m] - pc) + (cu[i - m] - pc)) +
-                                ((cu[i + m * RW] - pc) + (cu[i - m * RW] - pc));
-                acc = fmaf(W.c[m], d, acc);
-            }
-            float val = fmaf(kv, acc, 2.f * pc);
-            if (J->src_x == x && J->src_z == z) {
-#pragma clang fp contract(off)
-                const float srcv = J->src_scale * J->wavelet[L];
-                val = val + srcv;
-            }
-            const int dxs = sponge_depth(x, nx, nb), dz = sponge_depth(z, nz, nb);
-            pr[i] = leapfrog(val, pv, dxs * dxs + dz * dz, eta_dt);
-        }
-        __syncthreads();
-        float *tmp = cu;
-        cu = pr;
-        pr = tmp;
-        sample(cu, L + 1);
-    }
-
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-        const int i = ci[q], rx = i % RW, rz = i / RW;
-        if (!cin[q] || rx < A || rx >= A + OX || rz < A || rz >= A + OZ) continue;
-        const int64_t off = (int64_t)(cz[q] + M) * p64 + (cx[q] + M);
-        o1[off] = cu[i];
-        o0[off] = pr[i];
-    }
-}
-
 // Final receiver sampling (level n = n0 + step).
 __global__ void k_gather(const Job *__restrict__ jobs, const int *__restrict__ gprefix,
                          int njobs, int step, LevelMap lm)
@@ -1888,140 +730,51 @@ void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st)
     hipLaunchKernelGGL(k_vstats, dim3(vstats_blocks()), dim3(256), 0, st, v, n, partial);
 }
 
-// The 16th-order adjoint runs as two single-field passes (imaging condition,
-// then the psi update): the fused kernel carries two 17-plane queues in
-// more registers than fit 2 waves per SIMD, each pass one queue.  Both
-// compute bitwise the same values.  At 8th order the fused kernel is as
-// fast as the two passes and stays; FWI_SPLIT_ADJ=1 selects the two passes
-// there too.
-template <int M>
-static bool split_adjoint()
-{
-    if constexpr (M >= 8) {
-        return true;
-    } else if constexpr (M == 4) {
-        const char *e = getenv("FWI_SPLIT_ADJ");
-        return e && atoi(e) != 0;
-    } else {
-        return false;
-    }
-}
+// 3-D step launches, one definition per stencil radius (fwi_step3d.hip); 2-D
+// ones in fwi_step2d.hip.
+#define FWI_STEP3D_DECL(m)                                                                       \
+    void launch_step3d_m##m(int nw, bool adj, const Job *jobs, const int *prefix, int njobs,     \
+                            int step, int ttiles, int grid, int remap, const LevelMap &lm,       \
+                            hipStream_t st);                                                     \
+    hipError_t occupancy_step3d_m##m(int nw, bool adj, int *n);
+FWI_STEP3D_DECL(1)
+FWI_STEP3D_DECL(2)
+FWI_STEP3D_DECL(4)
+FWI_STEP3D_DECL(8)
+#undef FWI_STEP3D_DECL
+void launch_step2d(int M, int nw, bool adj, const Job *jobs, const int *prefix, int njobs,
+                   int step, int ttiles, int grid, int remap, const LevelMap &lm, hipStream_t st);
 
-template <int M, int NW, int RY>
-static void launch_3d(bool adj, const Job *jobs, const int *prefix, int njobs, int step,
-                      int ttiles, int grid, int remap, const LevelMap &lm, hipStream_t st)
-{
-    const dim3 g(grid), b(64 * NW);
-    if (!adj) {
-        hipLaunchKernelGGL((k_step3d<M, kFwd, NW, RY>), g, b, 0, st, jobs, prefix, njobs, step,
-                           ttiles, remap, lm);
-        return;
-    }
-    if constexpr (M >= 4) {
-        if (split_adjoint<M>()) {
-            // the imaging pass reads psi^{k+1} and p^k, which the psi pass leaves intact
-            hipLaunchKernelGGL((k_step3d<M, kImage, NW, RY>), g, b, 0, st, jobs, prefix, njobs,
-                               step, ttiles, remap, lm);
-            hipLaunchKernelGGL((k_step3d<M, kAdjPsi, NW, RY>), g, b, 0, st, jobs, prefix, njobs,
-                               step, ttiles, remap, lm);
-            return;
-        }
-    }
-    if constexpr (M < 8)
-        hipLaunchKernelGGL((k_step3d<M, kAdj, NW, RY>), g, b, 0, st, jobs, prefix, njobs, step,
-                           ttiles, remap, lm);
-}
-
-template <int M, int NW, int RY>
-static hipError_t occupancy_3d(int *n, bool adj)
-{
-    const int t = 64 * NW;
-    if (!adj) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_step3d<M, kFwd, NW, RY>, t, 0);
-    if constexpr (M >= 4) {
-        if (split_adjoint<M>()) {
-            int a = 0, c = 0;
-            hipError_t e =
-                hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_step3d<M, kAdjPsi, NW, RY>, t, 0);
-            if (e == hipSuccess)
-                e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c, k_step3d<M, kImage, NW, RY>, t, 0);
-            *n = a < c ? a : c;
-            return e;
-        }
-    }
-    if constexpr (M < 8)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_step3d<M, kAdj, NW, RY>, t, 0);
-    return hipErrorInvalidValue;
-}
-
-template <int M>
-static void launch_step_m(int ndim, int nw, bool adj, const Job *jobs, const int *prefix,
-                          int njobs, int step, int ttiles, int gblocks, int remap,
-                          const LevelMap &lm, hipStream_t st)
-{
-    const int grid = ttiles + (adj ? 0 : gblocks);
-    if (grid <= 0) return;
-    if (ndim == 3) {
-        switch (nw) {   // wavefronts per block x rows per thread
-        case 8: launch_3d<M, 8, 4>(adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
-        case 42: launch_3d<M, 4, 2>(adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
-        case 82: launch_3d<M, 8, 2>(adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
-        default: launch_3d<M, 4, 4>(adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
-        }
-    } else if (nw == 1) {   // one-row tiles, one cell per lane
-        if (adj)
-            hipLaunchKernelGGL((k_step2d_direct<M, true>), dim3(grid), dim3(64), 0, st, jobs,
-                               prefix, njobs, step, ttiles, remap, lm);
-        else
-            hipLaunchKernelGGL((k_step2d_direct<M, false>), dim3(grid), dim3(64), 0, st, jobs,
-                               prefix, njobs, step, ttiles, remap, lm);
-    } else {
-        if (adj)
-            hipLaunchKernelGGL((k_step2d<M, true>), dim3(grid), dim3(64), 0, st, jobs, prefix,
-                               njobs, step, ttiles, remap, lm);
-        else
-            hipLaunchKernelGGL((k_step2d<M, false>), dim3(grid), dim3(64), 0, st, jobs, prefix,
-                               njobs, step, ttiles, remap, lm);
-    }
-}
-
-// Resident blocks per CU of a step kernel (0 if the query fails).
-template <int M>
-static int occupancy_m(int ndim, int nw, bool adj)
+// Resident blocks per CU of a 3-D step kernel (0 if the query fails).
+int step_blocks_per_cu(int M, int nw, bool adj)
 {
     int n = 0;
-    hipError_t e = hipSuccess;
-    if (ndim == 3) {
-        if (nw == 8) e = occupancy_3d<M, 8, 4>(&n, adj);
-        else if (nw == 42) e = occupancy_3d<M, 4, 2>(&n, adj);
-        else if (nw == 82) e = occupancy_3d<M, 8, 2>(&n, adj);
-        else e = occupancy_3d<M, 4, 4>(&n, adj);
-    } else {
-        e = adj ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step2d<M, true>, 64, 0)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step2d<M, false>, 64, 0);
+    hipError_t e = hipErrorInvalidValue;
+    switch (M) {
+    case 1: e = occupancy_step3d_m1(nw, adj, &n); break;
+    case 2: e = occupancy_step3d_m2(nw, adj, &n); break;
+    case 4: e = occupancy_step3d_m4(nw, adj, &n); break;
+    case 8: e = occupancy_step3d_m8(nw, adj, &n); break;
+    default: break;
     }
     return e == hipSuccess ? n : 0;
-}
-
-int step_blocks_per_cu(int ndim, int M, int nw, bool adj)
-{
-    switch (M) {
-    case 1: return occupancy_m<1>(ndim, nw, adj);
-    case 2: return occupancy_m<2>(ndim, nw, adj);
-    case 4: return occupancy_m<4>(ndim, nw, adj);
-    case 8: return occupancy_m<8>(ndim, nw, adj);
-    default: return 0;
-    }
 }
 
 void launch_step(int ndim, int M, int nw, bool adj, const Job *jobs, const int *prefix,
                  int njobs, int step, int ttiles, int gblocks, int remap, const LevelMap &lm,
                  hipStream_t st)
 {
+    const int grid = ttiles + (adj ? 0 : gblocks);
+    if (grid <= 0) return;
+    if (ndim == 2) {
+        launch_step2d(M, nw, adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st);
+        return;
+    }
     switch (M) {
-    case 1: launch_step_m<1>(ndim, nw, adj, jobs, prefix, njobs, step, ttiles, gblocks, remap, lm, st); break;
-    case 2: launch_step_m<2>(ndim, nw, adj, jobs, prefix, njobs, step, ttiles, gblocks, remap, lm, st); break;
-    case 4: launch_step_m<4>(ndim, nw, adj, jobs, prefix, njobs, step, ttiles, gblocks, remap, lm, st); break;
-    case 8: launch_step_m<8>(ndim, nw, adj, jobs, prefix, njobs, step, ttiles, gblocks, remap, lm, st); break;
+    case 1: launch_step3d_m1(nw, adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
+    case 2: launch_step3d_m2(nw, adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
+    case 4: launch_step3d_m4(nw, adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
+    case 8: launch_step3d_m8(nw, adj, jobs, prefix, njobs, step, ttiles, grid, remap, lm, st); break;
     default: break;
     }
 }
@@ -2090,34 +843,6 @@ void launch_snapshot(const Job *jobs, int njobs, int64_t fstride, int slot, int 
     hipLaunchKernelGGL(k_snapshot, dim3(grid_for(fstride / 4, 256, 4096), 2 * njobs), dim3(256),
                        0, st, jobs, slot, time, dir, mask, lm);
 }
-
-// Multi-step 2-D forward launches: the largest step count per launch, the
-// output tile, and the launch itself (M <= 4).
-int multi2d_steps() { return 4; }
-void multi2d_tile(int M, int *ox, int *oz)
-{
-    switch (M) {
-    case 1: *ox = Multi2d<1, 4>::OX; break;
-    case 2: *ox = Multi2d<2, 4>::OX; break;
-    default: *ox = Multi2d<4, 4>::OX; break;
-    }
-    *oz = Multi2d<4, 4>::OZ;
-}
-void launch_step2d_multi(int M, const Job *jobs, int njobs, int tiles_per_job, int ntxm,
-                         int step, int kk, bool record, hipStream_t st)
-{
-    // 1024 threads: three cells of the 64 x 48 region per thread and step, so
-    // a step is a short latency chain (256 threads: 5.3 us per step)
-    const dim3 g(njobs * tiles_per_job), b(1024);
-    const int rec = record ? 1 : 0;
-    switch (M) {
-    case 1: hipLaunchKernelGGL((k_step2d_multi<1, 4>), g, b, 0, st, jobs, tiles_per_job, ntxm, step, kk, rec); break;
-    case 2: hipLaunchKernelGGL((k_step2d_multi<2, 4>), g, b, 0, st, jobs, tiles_per_job, ntxm, step, kk, rec); break;
-    case 4: hipLaunchKernelGGL((k_step2d_multi<4, 4>), g, b, 0, st, jobs, tiles_per_job, ntxm, step, kk, rec); break;
-    default: break;
-    }
-}
-
 void launch_gather(const Job *jobs, const int *gprefix, int njobs, int gblocks, int threads,
                    int step, const LevelMap &lm, hipStream_t st)
 {

@@ -46,7 +46,7 @@ void launch_fold(int ndim, const Job *jobs, int njobs, int M, int gy, int nz, in
                  int nb, int nzm, int nym, int nxm, float *tmp1, float *tmp2, const float *v,
                  float *dv, hipStream_t st);
 int vstats_blocks();
-int step_blocks_per_cu(int ndim, int M, int nw, bool adj);
+int step_blocks_per_cu(int M, int nw, bool adj);
 void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st);
 void launch_nonfinite_level(const Job *jobs, int njobs, int L, float *partial, hipStream_t st);
 void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *levels,
@@ -398,7 +398,7 @@ void tiles_for(const Geometry &g, int njobs, bool adj, int *ntx, int *nty, int *
                 cus = prop.multiProcessorCount;
             if (cus <= 0) cus = 256;
         }
-        const int occ = std::max(1, step_blocks_per_cu(3, g.M, code, adj));
+        const int occ = std::max(1, step_blocks_per_cu(g.M, code, adj));
         int64_t slots = (int64_t)occ * cus;
         if (const char *e = getenv("FWI_TARGET_BLOCKS")) slots = std::max(1, atoi(e));
         double best = 0.0;
