@@ -125,8 +125,8 @@ __device__ __forceinline__ float adj_source(const Job *__restrict__ J, int k, in
 __device__ __forceinline__ float leapfrog(float val, float prev, int d2, float eta_dt)
 {
     if (d2 == 0) return val - prev;
-    const float e = eta_dt * (float)d2;
-    return __builtin_amdgcn_rcpf(1.f + e) * fmaf(-(1.f - e), prev, val);
+    return __builtin_amdgcn_rcpf(fmaf(eta_dt, (float)d2, 1.f)) *
+           fmaf(-fmaf(-eta_dt, (float)d2, 1.f), prev, val);
 }
 
 // Streams read or written once per launch (kappa', the previous level, the

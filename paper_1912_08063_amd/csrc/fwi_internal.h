@@ -73,11 +73,12 @@ struct Job {
     const int64_t *rec_off;    // [nrec] field offsets of the receiver cells
     const int32_t *rec_next;   // [nrec] next receiver on the same cell, -1 at the end
     const int32_t *rec_head;   // [nrec] 1 for the first receiver of its cell
-    // 2-D adjoint source: the first receiver of each receiver cell, grouped
-    // by the adjoint tile that holds the cell and sorted by row within it;
-    // tile t (local index) owns entries rt_start[t] .. rt_start[t+1]-1 of
-    // rt_rec (receiver) and rt_key (row << 6 | column within the tile)
-    const int32_t *rt_start;   // [adjoint tiles + 1] (2-D jobs only)
+    // 2-D receiver lists: the first receiver of each receiver cell, sorted by
+    // 64-column tile and row; rows z0 .. z1-1 of column tile t own entries
+    // rt_start[t nz + z0] .. rt_start[t nz + z1] - 1 of rt_rec (receiver) and
+    // rt_key (row << 6 | column within the tile)
+    int32_t rec_z0, rec_z1;    // padded rows that hold receivers (2-D): [rec_z0, rec_z1)
+    const int32_t *rt_start;   // [column tiles * nz + 1] (2-D jobs only)
     const int32_t *rt_rec;     // [receiver cells]
     const int32_t *rt_key;     // [receiver cells]
     float *traces;         // [nt][nrec]
@@ -96,6 +97,61 @@ struct LevelMap {
     int32_t lev[3] = {kNoLevel, kNoLevel, kNoLevel};
     int32_t fld[3] = {0, 0, 0};
 };
+
+// Column (row) tiles of a multi-step 2-D launch: regions of `w` cells, each
+// overlapping the next by its two aprons of `a` cells, over `cells` memory
+// columns (rows, frames included).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int tb_tiles(int cells, int w, int a)
+{
+    return cells <= w ? 1 : (cells - w + (w - 2 * a) - 1) / (w - 2 * a) + 1;
+}
+
+// One multi-step 2-D launch.
+
+struct TbLaunch {
+    int32_t tiles_per_job;   // jobs of one grid and level (0: the prefix array's)
+    uint32_t magic_job, magic_tx;   // tb_magic of tiles_per_job and ntx
+    int32_t ntx, ntz;        // tiles in x and z (tiles_per_job > 0)
+    int32_t step;            // the level itself (tiles_per_job > 0), or the chunk's step
+    int32_t kk;              // steps
+    int32_t A;               // apron
+    int32_t pair;            // fields to read: adjoint pair, forward pair (-1: ring)
+    int32_t remap, record, store_all;
+};
+
+// Two-step marching 2-D launches address a field by 32-bit byte offsets and
+// take an offset of this size as outside it.
+constexpr int32_t kPipeFieldBytes = 1 << 30;
+
+// One two-step marching 2-D launch: chunks of zc rows; ring slots of levels n,
+// n-1, n+1, n+2.
+struct PipeLaunch {
+    int32_t tiles_per_job;
+    uint32_t magic_job, magic_tx;
+    int32_t ntx, zc, n;
+    int32_t slot[4];
+    int32_t gblocks;         // trace blocks per job
+    int32_t remap;
+};
+
+// Kernel shapes of multi-step 2-D launches (see tb_config) that are built for a
+// stencil radius.
+constexpr int kTbShapes = 5;
+constexpr bool tb_has_shape(int M, int shape)
+{
+    return M == 8 ? shape == 0 || shape == 1 || shape == 4 : shape >= 0 && shape <= 3;
+}
+
+// ceil(2^32 / d), for which umulhi(b, magic) = b / d while b d < 2^32 (0 where
+// b may be larger, or d is 1).
+inline uint32_t tb_magic(int64_t d, int64_t bmax)
+{
+    return d < 2 || bmax * d >= (int64_t(1) << 32)
+               ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)d - 1) / (uint64_t)d);
+}
 
 // Launch tables of fwi_jobs_advance, assembled on the device (k_assemble):
 // each entry is copied from the job's own table entry in its memory and its

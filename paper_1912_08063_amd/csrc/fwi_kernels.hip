@@ -21,7 +21,8 @@
 //    the current xy plane with its M-cell halo is staged in LDS for the x and
 //    y derivatives, and each thread owns 4 (or 2) consecutive y rows so
 //    y-neighbours are reused from LDS.
-//  * 2-D: one wavefront per block, 64 columns marching down a chunk of rows.
+//  * 2-D: one wavefront per block, 64 columns marching down a chunk of rows;
+//    runs of consecutive steps take several steps per launch (fwi_step2d.hip).
 //  * Each wavefront reads and writes whole aligned 256-byte row segments.
 //  * Blocks are remapped so that each XCD (one L2 each) gets a contiguous
 //    range of tiles: neighbouring tiles share their halos in the same L2.
@@ -656,17 +657,17 @@ __global__ __launch_bounds__(64) void k_assemble(AssembleArgs a, Job *__restrict
     }
 }
 
-// Non-finite cells of forward level L of every job (ring slot L mod R):
+// Non-finite cells of one ring field (slot) of every job:
 // per-block counts, partial[0 .. gridDim.x), summed on the host.
 __global__ __launch_bounds__(256) void k_nonfinite_level(const Job *__restrict__ jobs, int njobs,
-                                                         int L, float *__restrict__ partial)
+                                                         int slot, float *__restrict__ partial)
 {
     __shared__ float red[256];
     float bad = 0.f;
     for (int j = 0; j < njobs; ++j) {
         const Job *J = jobs + j;
         const float4 *f =
-            reinterpret_cast<const float4 *>(J->ring + (int64_t)mod_pos(L, J->R) * J->fstride);
+            reinterpret_cast<const float4 *>(J->ring + (int64_t)slot * J->fstride);
         const int64_t n4 = J->fstride / 4;
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
              i += (int64_t)gridDim.x * blockDim.x) {
@@ -719,10 +720,10 @@ void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *le
                        prefix, levels);
 }
 
-void launch_nonfinite_level(const Job *jobs, int njobs, int L, float *partial, hipStream_t st)
+void launch_nonfinite_level(const Job *jobs, int njobs, int slot, float *partial, hipStream_t st)
 {
     hipLaunchKernelGGL(k_nonfinite_level, dim3(vstats_blocks()), dim3(256), 0, st, jobs, njobs,
-                       L, partial);
+                       slot, partial);
 }
 
 void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st)

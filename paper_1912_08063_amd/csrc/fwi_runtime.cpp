@@ -48,13 +48,17 @@ void launch_fold(int ndim, const Job *jobs, int njobs, int M, int gy, int nz, in
 int vstats_blocks();
 int step_blocks_per_cu(int M, int nw, bool adj);
 void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st);
-void launch_nonfinite_level(const Job *jobs, int njobs, int L, float *partial, hipStream_t st);
+void launch_nonfinite_level(const Job *jobs, int njobs, int slot, float *partial, hipStream_t st);
 void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *levels,
                      hipStream_t st);
-int multi2d_steps();
-void multi2d_tile(int M, int *ox, int *oz);
-void launch_step2d_multi(int M, const Job *jobs, int njobs, int tiles_per_job, int ntxm,
-                         int step, int kk, bool record, hipStream_t st);
+int tb2d_width(int shape);
+int tb2d_height(int shape);
+void launch_step2d_tb(int M, int shape, bool adj, const Job *jobs, const int *prefix, int njobs,
+                      int ttiles, const TbLaunch &a, hipStream_t st);
+int pipe2d_width();
+int pipe2d_group(int M);
+void launch_step2d_pipe(int M, const Job *jobs, int njobs, const PipeLaunch &a, hipStream_t st);
+void launch_gather2(const Job *jobs, int njobs, int nrec, int n, int s0, int s1, hipStream_t st);
 int scratch_address(void **ptr);
 void launch_stream_probe(const float *a, const float *b, const float *c, float *o, int64_t n,
                          int variant, hipStream_t st);
@@ -202,15 +206,27 @@ struct Policy {
     int R = 2;       // forward ring length
     int nsnap = 0;   // snapshot slots per shot
     int ctop = 0;    // EVERY / ALL: base of the segment kept in the ring
+    // 2-D: several steps per launch, at most tb_steps forward and adj_steps
+    // adjoint ones, in kernel shape tb_shape (0 steps: one step per launch)
+    int tb_steps = 0, adj_steps = 0, tb_shape = 0;
 };
 
-bool multi_2d(const Geometry &g, int njobs);
+struct TbConfig {
+    int shape, steps;
+};
+TbConfig tb_config(const Geometry &g, int njobs);
 
-int make_policy(const fwi_problem *p, const Geometry &g, int mode, const fwi_ckpt *ck, Policy *po)
+// tb: whether several 2-D steps may share a launch (they need two more fields)
+int make_policy(const fwi_problem *p, const Geometry &g, int mode, const fwi_ckpt *ck, Policy *po,
+                bool tb = true)
 {
     *po = Policy{};
+    const TbConfig tc = tb ? tb_config(g, p->nshots) : TbConfig{0, 0};
+    const int tbk = tc.steps;
+    po->tb_shape = tc.shape;
     if (mode == FWI_MODE_FORWARD) {
-        po->R = multi_2d(g, p->nshots) ? multi2d_steps() + 2 : 2;
+        po->tb_steps = tbk;
+        po->R = tbk > 0 ? 4 : 2;   // two pairs of levels, read and written in turn
         return FWI_OK;
     }
     if (!ck) return fail(FWI_EINVAL, "checkpoint policy is NULL");
@@ -227,6 +243,9 @@ int make_policy(const fwi_problem *p, const Geometry &g, int mode, const fwi_ckp
         po->R = K + 1;
         po->ctop = K * ((nt - 1) / K);
         po->nsnap = std::max(0, po->ctop / K - 1);
+        // a launch's input levels n, n-1 and output levels differ in the ring
+        po->tb_steps = std::min(tbk, po->R - 2);
+        po->adj_steps = po->tb_steps > 0 ? tbk : 0;
         return FWI_OK;
     }
     case FWI_CKPT_REVOLVE: {
@@ -295,7 +314,7 @@ void make_layout(const fwi_problem *p, const Geometry &g, const Policy &po, int 
     L->vstats = w.take(sizeof(float) * 3ull * vstats_blocks());
     if (mode == FWI_MODE_BACKWARD || mode == FWI_MODE_GRADIENT) {
         L->has_adj = true;
-        L->adj = w.take(2 * fb * S);
+        L->adj = w.take((po.adj_steps > 0 ? 4 : 2) * fb * S);
         L->grad = w.take(fb * S);
         L->has_fold = true;
         L->fold1 = w.take(sizeof(float) * (uint64_t)g.nz * g.ny * g.nxm);
@@ -353,15 +372,72 @@ bool direct_2d(const Geometry &g, int njobs)
     if (const char *e = getenv("FWI_DIRECT2D")) return atoi(e) != 0;
     return (int64_t)njobs * g.nz * g.nx <= kDirect2dCells;
 }
-// Forward-only calls on such grids (up to 8th order) advance several steps
-// per launch (k_step2d_multi); their ring holds K + 2 levels so that a
-// launch's input slots (n, n-1) and output slots (n+kk, n+kk-1) differ.
-// FWI_MULTI2D=0 keeps one step per launch.
-bool multi_2d(const Geometry &g, int njobs)
+// Several steps per launch (k_step2d_tb) wherever consecutive steps need no
+// level in between: forward sweeps and their recomputation, and adjoint
+// sweeps.  Shape (region, rows per thread) and steps by the cells that one
+// launch updates: small launches are bound by latency, so their regions are
+// small (one block per CU, many steps per launch); larger ones by the
+// arithmetic, so by the share of the region that the apron of steps x M cells
+// takes.  Measured, us per 240-step gradient with every-50 checkpoints, 8th
+// order (other shapes in turn; one step per launch last): 128 x 128: 48 x 40
+// with 4 steps 1359 (64 x 48 1468, 64 x 64 1609; 2400); 256 x 256: 64 x 48 with 4
+// 1507 (48 x 40 with 3 1602, 64 x 64 1644; 2517); 1024 x 320: 64 x 64 with 3 2275
+// (64 x 48 with 2 2357, 128 x 64 with 4 2506; 3743); three such shots: 128 x 64
+// with 4 4388 (64 x 64 4701; 7597).  At 16th order the apron leaves two steps:
+// 128 x 128: 2040 against 2675, and 1024 x 320 is fastest with one (4119 against
+// 4267); four shots of 303 x 555: 128 x 64 with four rows per thread 7185 us per
+// training step against 9347.
+// FWI_MULTI2D=0, or FWI_DIRECT2D=0, keeps one step per launch; FWI_TB2D names a
+// shape.
+TbConfig tb_config(const Geometry &g, int njobs)
 {
-    if (g.ndim != 2 || g.M > 4 || !direct_2d(g, njobs)) return false;
-    const char *e = getenv("FWI_MULTI2D");
-    return !e || atoi(e) != 0;
+    const TbConfig none{0, 0};
+    if (g.ndim != 2) return none;
+    if (const char *e = getenv("FWI_MULTI2D"))
+        if (atoi(e) == 0) return none;
+    if (const char *e = getenv("FWI_DIRECT2D"))
+        if (atoi(e) == 0) return none;
+    // two more fields per shot, up to 4 GiB
+    if (2 * g.fstride * (int64_t)sizeof(float) * njobs > (int64_t(4) << 30)) return none;
+    const int64_t cells = (int64_t)njobs * g.nz * g.nx;
+    TbConfig c;
+    if (g.M >= 8) {
+        if (cells > 300000 && (cells <= 600000 || cells > kDirect2dCells)) c = none;
+        else c = TbConfig{cells <= 60000 ? 0 : cells <= 300000 ? 1 : 4, 2};
+    } else {
+        const bool wide = g.M == 4;
+        c.shape = cells <= 60000 ? 0 : cells <= 300000 ? 1 : cells <= 700000 ? (wide ? 2 : 1) : 3;
+        if (wide) c.steps = c.shape == 2 ? 3 : 4;
+        else if (g.M == 2) c.steps = cells <= 60000 ? 8 : cells <= 300000 ? 6 : 4;
+        else c.steps = 8;
+    }
+    if (const char *e = getenv("FWI_TB2D")) {
+        const int v = atoi(e);
+        if (v >= 0 && v < kTbShapes && tb_has_shape(g.M, v)) {
+            c.shape = v;
+            if (c.steps == 0) c.steps = 2;
+        }
+    }
+    return c;
+}
+// Apron of a launch of up to `steps` steps: whole patches (4 columns, rows)
+int tb_apron(const Geometry &g, int steps) { return (steps * g.M + 3) / 4 * 4; }
+
+// Rows per chunk of two-step marching forward launches (0: k_step2d_tb): from
+// 2.5 M cells (8 shots of 1064 x 360: 3129 against 3203 us per 300 steps; 16:
+// 4666 against 5755; 4: 2231 against 1909), the longest chunks of up to 48 rows
+// that give 2048 waves (32 shots: 48 rows 14.3 ms, 36 16.6, 24 15.2; 16 shots:
+// 24 rows 4666 us, 48 5587, 12 5018).  Fields are addressed by 32-bit offsets.
+// FWI_PIPE2D sets the rows (0: off).
+int pipe_rows(const Geometry &g, int njobs, int ntx)
+{
+    if ((g.M != 2 && g.M != 4) || g.fstride * (int64_t)sizeof(float) >= kPipeFieldBytes) return 0;
+    const int u = pipe2d_group(g.M);
+    if (const char *e = getenv("FWI_PIPE2D")) return std::max(0, (atoi(e) + u - 1) / u * u);
+    if ((int64_t)njobs * g.nz * g.nx < 2500000) return 0;
+    int zc = 48 / u * u;
+    while (zc > u && (int64_t)ntx * njobs * ((g.nz + zc - 1) / zc) < 2048) zc -= u;
+    return zc;
 }
 
 int block_waves(int code) { return code == 8 || code == 82 ? 8 : 4; }
@@ -467,10 +543,13 @@ struct Ctx {
     int ttiles = 0, atiles = 0, gblocks = 0, gthreads = 64;
     int remap = 1;
     int nw = 4, nw_adj = 42;
-    // forward-only small 2-D calls: several steps per launch over
-    // mtiles = mntx x (rows of tiles) output tiles per shot
-    bool multi = false;
-    int mtiles = 0, mntx = 0;
+    // several 2-D steps per launch: apron and tiles per shot of forward (0) and
+    // adjoint (1) launches; the pair of fields that holds the newest forward
+    // (FORWARD mode) and adjoint levels
+    int tb_apron[2] = {0, 0}, tb_ntx[2] = {0, 0}, tb_ntz[2] = {0, 0};
+    int fwd_pair = 0, adj_pair = 0;
+    // two-step marching forward launches: column tiles, rows per chunk (0: none)
+    int pipe_ntx = 0, pipe_zc = 0;
     std::vector<int> slot_time;
     // plan mode (host only): launches are recorded here instead of issued,
     // ten int32 per launch (see fwi_revolve_plan)
@@ -483,12 +562,12 @@ struct Ctx {
 };
 
 int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws,
-            uint64_t ws_bytes, void *ckbuf, uint64_t ck_bytes, void *stream)
+            uint64_t ws_bytes, void *ckbuf, uint64_t ck_bytes, void *stream, bool tb = true)
 {
     int st = make_geometry(p, &c.g);
     if (st) return st;
     c.p = p;
-    st = make_policy(p, c.g, mode, ck, &c.po);
+    st = make_policy(p, c.g, mode, ck, &c.po, tb);
     if (st) return st;
     make_layout(p, c.g, c.po, mode, &c.L);
     if (!ws) return fail(FWI_EINVAL, "workspace is NULL");
@@ -512,13 +591,16 @@ int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws
     c.nw = shape_code(false, c.g.M);
     c.nw_adj = shape_code(true, c.g.M);
     if (c.g.ndim == 2) c.nw = c.nw_adj = direct_2d(c.g, p->nshots) ? 1 : 4;
-    c.multi = mode == FWI_MODE_FORWARD && multi_2d(c.g, p->nshots) &&
-              c.po.R == multi2d_steps() + 2;
-    if (c.multi) {
-        int ox = 0, oz = 0;
-        multi2d_tile(c.g.M, &ox, &oz);
-        c.mntx = (c.g.nx + ox - 1) / ox;
-        c.mtiles = c.mntx * ((c.g.nz + oz - 1) / oz);
+    for (int a = 0; a < 2; ++a) {
+        const int steps = a ? c.po.adj_steps : c.po.tb_steps;
+        if (steps <= 0) continue;
+        c.tb_apron[a] = tb_apron(c.g, steps);
+        c.tb_ntx[a] = tb_tiles(c.g.nx + 2 * c.g.M, tb2d_width(c.po.tb_shape), c.tb_apron[a]);
+        c.tb_ntz[a] = tb_tiles(c.g.nz + 2 * c.g.M, tb2d_height(c.po.tb_shape), c.tb_apron[a]);
+    }
+    if (c.po.tb_steps >= 2) {
+        c.pipe_ntx = tb_tiles(c.g.nx + 2 * c.g.M, pipe2d_width(), 2 * c.g.M);
+        c.pipe_zc = pipe_rows(c.g, p->nshots, c.pipe_ntx);
     }
     return FWI_OK;
 }
@@ -611,8 +693,8 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     int64_t *d_roff = reinterpret_cast<int64_t *>(c.ws + c.L.rec_off);
     int32_t *d_rnext = reinterpret_cast<int32_t *>(c.ws + c.L.rec_next);
     int32_t *d_rhead = reinterpret_cast<int32_t *>(c.ws + c.L.rec_head);
-    // 2-D adjoint source lists: each receiver cell (its first receiver) under
-    // the adjoint tile that stores it, sorted by tile and then by row
+    // 2-D receiver lists: each receiver cell (its first receiver), sorted by
+    // 64-column tile and row
     const bool lists = D == 2;
     const uint64_t mt = lists ? max_adj_tiles_2d(g) + 1 : 0;
     int32_t *d_rtstart = lists ? reinterpret_cast<int32_t *>(c.ws + c.L.rt_start) : nullptr;
@@ -620,8 +702,8 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     int32_t *d_rtkey = lists ? reinterpret_cast<int32_t *>(c.ws + c.L.rt_key) : nullptr;
     std::vector<int32_t> rtstart((size_t)S * mt, 0), rtrec(lists ? (size_t)S * R : 0);
     std::vector<int32_t> rtkey(rtrec.size());
+    std::vector<int32_t> rz0(S, g.nz), rz1(S, 0);   // rows that hold receivers
     if (lists) {
-        const Job::Tiling &T = til[1];
         std::vector<std::pair<int64_t, int32_t>> key;
         for (int s = 0; s < S; ++s) {
             key.clear();
@@ -629,18 +711,19 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
                 if (!rhead[(size_t)s * R + r]) continue;
                 const int64_t off = roff[(size_t)s * R + r];
                 const int zr = (int)(off / g.pitch) - g.M, cr = (int)(off % g.pitch);
-                const int64_t tile = (int64_t)(zr / T.zc) * T.ntx + cr / kTileX;
-                key.push_back({(tile * (int64_t)(g.nz + 1) + zr) * kTileX + cr % kTileX, r});
+                rz0[s] = std::min(rz0[s], zr);
+                rz1[s] = std::max(rz1[s], zr + 1);
+                key.push_back({((int64_t)(cr / kTileX) * g.nz + zr) * kTileX + cr % kTileX, r});
             }
-            std::stable_sort(key.begin(), key.end());
+            std::sort(key.begin(), key.end());   // one entry per cell: keys differ
             int32_t *st = &rtstart[(size_t)s * mt];
             int32_t *lst = &rtrec[(size_t)s * R];
             int32_t *kk = &rtkey[(size_t)s * R];
             for (size_t i = 0; i < key.size(); ++i) {
-                const int64_t tz = key[i].first / kTileX;   // tile * (nz + 1) + row
+                const int64_t tz = key[i].first / kTileX;   // tile * nz + row
                 lst[i] = key[i].second;
-                kk[i] = (int32_t)((tz % (g.nz + 1)) << 6 | (key[i].first % kTileX));
-                st[tz / (g.nz + 1) + 1] += 1;
+                kk[i] = (int32_t)((tz % g.nz) << 6 | (key[i].first % kTileX));
+                st[tz + 1] += 1;
             }
             for (uint64_t t = 1; t < mt; ++t) st[t] += st[t - 1];
         }
@@ -668,7 +751,7 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
         J.kappa = kappa;
         J.ring = ring + (uint64_t)s * c.po.R * fs;
         J.R = c.po.R;
-        J.adj = adj ? adj + (uint64_t)s * 2 * fs : nullptr;
+        J.adj = adj ? adj + (uint64_t)s * (c.po.adj_steps > 0 ? 4 : 2) * fs : nullptr;
         J.grad = grad ? grad + (uint64_t)s * fs : nullptr;
         J.snap = c.po.nsnap > 0 ? snap + (uint64_t)s * 2 * c.po.nsnap * fs : nullptr;
         const int32_t *q = &hs[(size_t)s * D];
@@ -680,6 +763,8 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
         J.rec_off = d_roff + (size_t)s * R;
         J.rec_next = d_rnext + (size_t)s * R;
         J.rec_head = d_rhead + (size_t)s * R;
+        J.rec_z0 = lists ? rz0[s] : 0;
+        J.rec_z1 = lists ? rz1[s] : 0;
         J.rt_start = lists ? d_rtstart + (size_t)s * mt : nullptr;
         J.rt_rec = lists ? d_rtrec + (size_t)s * R : nullptr;
         J.rt_key = lists ? d_rtkey + (size_t)s * R : nullptr;
@@ -751,6 +836,105 @@ int adj_step(Ctx &c, int k, const LevelMap &lm = LevelMap{})
     if (c.g.ndim == 3)   // 2-D adjoint steps add the adjoint source themselves
         launch_adj_inject(c.d_jobs, c.d_prefix + c.p->nshots + 1, c.p->nshots, c.gblocks,
                           c.gthreads, -k, c.st);
+    return FWI_OK;
+}
+
+// Multi-step 2-D launch of every shot: kk steps from level n (adjoint: down
+// from it).
+void tb_launch(Ctx &c, bool adj, int n, int kk, int pair, bool record, bool store_all)
+{
+    const int S = c.p->nshots, T = c.tb_ntx[adj] * c.tb_ntz[adj];
+    TbLaunch a{};
+    a.tiles_per_job = T;
+    a.magic_job = tb_magic(T, (int64_t)T * S);
+    a.magic_tx = tb_magic(c.tb_ntx[adj], T);
+    a.ntx = c.tb_ntx[adj];
+    a.ntz = c.tb_ntz[adj];
+    a.step = n;
+    a.kk = kk;
+    a.A = c.tb_apron[adj];
+    a.pair = pair;
+    a.remap = c.remap;
+    a.record = record;
+    a.store_all = store_all;
+    launch_step2d_tb(c.g.M, c.po.tb_shape, adj, c.d_jobs, nullptr, S, T * S, a, c.st);
+}
+
+// Steps n = a .. b-1, several per 2-D launch where the call allows it
+// (po.tb_steps); store_all: every level is kept in the ring, otherwise only the
+// newest two are.
+int fwd_range(Ctx &c, int a, int b, bool record, bool store_all)
+{
+    if (c.po.tb_steps <= 0) {
+        for (int n = a; n < b; ++n) fwd_step(c, n, record);
+        return FWI_OK;
+    }
+    const bool pairs = c.po.every == 0;   // FORWARD mode: pairs of fields, not a ring
+    const int S = c.p->nshots, R = c.po.R;
+    int n = a;
+    if (c.pipe_zc > 0) {
+        PipeLaunch p{};
+        p.zc = c.pipe_zc;
+        p.ntx = c.pipe_ntx;
+        p.tiles_per_job = p.ntx * ((c.g.nz + p.zc - 1) / p.zc);
+        p.magic_job = tb_magic(p.tiles_per_job, (int64_t)p.tiles_per_job * S);
+        p.magic_tx = tb_magic(p.ntx, p.tiles_per_job);
+        p.remap = c.remap;
+        // A range that keeps only its last two levels alternates between four
+        // fields, which stay in the Infinity Cache: in a ring, four slots that
+        // differ from those of levels a, a-1, b and b-1 (32 shots: 24 instead of
+        // 30 us per step).
+        const bool few = !pairs && !store_all && R >= 10 && b - a == R - 1;
+        auto ring = [&](int L) { return (L % R + R) % R; };
+        auto slot = [&](int L, bool end, int pair) {
+            if (pairs) return 2 * pair + (L & 1);
+            return few && !end ? ring(b + 2 + 2 * pair + (L & 1)) : ring(L);
+        };
+        int pair = pairs ? c.fwd_pair : 0;
+        for (; n + 2 <= b; n += 2) {
+            const bool last = n + 4 > b;
+            p.n = n;
+            p.slot[0] = slot(n, n == a, pair);
+            p.slot[1] = slot(n - 1, n == a, pair);
+            pair ^= 1;
+            p.slot[2] = slot(n + 1, last, pair);
+            p.slot[3] = slot(n + 2, last, pair);
+            // a launch samples the levels it reads
+            p.gblocks = record && n > a ? (c.p->nrec + 63) / 64 : 0;
+            launch_step2d_pipe(c.g.M, c.d_jobs, S, p, c.st);
+        }
+        if (pairs) c.fwd_pair = pair;
+        if (record && n > a)
+            launch_gather2(c.d_jobs, S, c.p->nrec, n, slot(n, true, pair), slot(n - 1, true, pair),
+                           c.st);
+        if (n < b && !pairs) {   // a last single step, in the ring
+            fwd_step(c, n, false);
+            ++n;
+            if (record) launch_gather2(c.d_jobs, S, c.p->nrec, n, ring(n), ring(n - 1), c.st);
+        }
+    }
+    while (n < b) {
+        const int kk = std::min(b - n, c.po.tb_steps);
+        tb_launch(c, false, n, kk, pairs ? c.fwd_pair : -1, record, store_all);
+        if (pairs) c.fwd_pair ^= 1;
+        n += kk;
+    }
+    return FWI_OK;
+}
+
+// Adjoint steps k = hi .. lo.
+int adj_range(Ctx &c, int hi, int lo)
+{
+    if (c.po.adj_steps <= 0) {
+        for (int k = hi; k >= lo; --k) adj_step(c, k);
+        return FWI_OK;
+    }
+    for (int k = hi; k >= lo;) {
+        const int kk = std::min(k - lo + 1, c.po.adj_steps);
+        tb_launch(c, true, k, kk, c.adj_pair, false, false);
+        c.adj_pair ^= 1;
+        k -= kk;
+    }
     return FWI_OK;
 }
 
@@ -913,7 +1097,9 @@ int forward_phase(Ctx &c, bool record)
     const uint64_t fs = (uint64_t)c.g.fstride;
     if (!c.plan) {
         zero_frames(c, c.jobs[0].ring, (uint64_t)c.po.R * c.p->nshots);
-        TRY(snapshot(c, 0, 0, 2));   // levels 0 and -1: the zero initial state
+        // levels 0 and -1: the zero initial state (FORWARD mode on pairs of
+        // fields: the first pair, fields 0 and 1)
+        TRY(snapshot(c, 0, c.po.every == 0 && c.po.tb_steps > 0 ? 1 : 0, 2));
     }
     if (c.po.kind == FWI_CKPT_REVOLVE) {
         int64_t steps = 0;
@@ -948,27 +1134,18 @@ int forward_phase(Ctx &c, bool record)
         TRY(rv_to_ring(c, h, nt - 1));
         if (!c.plan) HIP_TRY(hipGetLastError());
         return FWI_OK;
-    } else if (c.multi && !c.plan) {
-        // up to multi2d_steps() steps per launch; a last single step runs alone
-        for (int n = 0; n < nt;) {
-            const int kk = std::min(nt - n, multi2d_steps());
-            if (kk >= 2) {
-                launch_step2d_multi(c.g.M, c.d_jobs, c.p->nshots, c.mtiles, c.mntx, n, kk, record,
-                                    c.st);
-            } else {
-                fwd_step(c, n, record);
-            }
-            n += kk;
-        }
+    } else if (c.po.every == 0) {
+        TRY(fwd_range(c, 0, nt, record, false));
     } else {
         const int K = c.po.every;
-        for (int n = 0; n < nt; ++n) {
-            fwd_step(c, n, record);
-            const int t = n + 1;
-            if (K > 0 && t % K == 0 && t <= c.po.ctop - K) TRY(snapshot(c, t / K - 1, t, 0));
+        for (int n = 0; n < nt; n += K) {
+            // the last segment's levels stay in the ring for the adjoint sweep
+            const int t = std::min(nt, n + K);
+            TRY(fwd_range(c, n, t, record, n >= c.po.ctop));
+            if (t % K == 0 && t <= c.po.ctop - K) TRY(snapshot(c, t / K - 1, t, 0));
         }
     }
-    if (record)
+    if (record && c.po.tb_steps <= 0)   // multi-step launches sample what they compute
         launch_gather(c.d_jobs, c.d_prefix + c.p->nshots + 1, c.p->nshots, c.gblocks,
                       c.gthreads, nt, LevelMap{}, c.st);
     HIP_TRY(hipGetLastError());
@@ -982,11 +1159,11 @@ int backward_phase(Ctx &c)
     const int nt = c.p->nt;
     const uint64_t fs = (uint64_t)c.g.fstride;
     if (!c.plan) {
-        zero(c.jobs[0].adj, 2 * fs * c.p->nshots, c.st);
+        zero(c.jobs[0].adj, (c.po.adj_steps > 0 ? 4 : 2) * fs * c.p->nshots, c.st);
         zero(c.jobs[0].grad, fs * c.p->nshots, c.st);
     }
-    adj_step(c, nt);
     if (c.po.kind == FWI_CKPT_REVOLVE) {
+        adj_step(c, nt);
         int64_t steps = 0;
         std::vector<Action> acts = revolve_schedule(nt, c.po.nsnap, &steps);
         c.slot_time.assign(std::max(c.po.nsnap, 1), -1);
@@ -1024,12 +1201,12 @@ int backward_phase(Ctx &c)
         }
     } else {
         const int K = c.po.every, ctop = c.po.ctop;
-        for (int k = nt - 1; k >= std::max(ctop, 1); --k) adj_step(c, k);
+        TRY(adj_range(c, nt, std::max(ctop, 1)));
         for (int base = ctop - K; base >= 0; base -= K) {
             if (base == 0) TRY(snapshot(c, 0, 0, 2));
             else TRY(snapshot(c, base / K - 1, base, 1));
-            for (int n = base; n < base + K - 1; ++n) fwd_step(c, n, false);
-            for (int k = base + K - 1; k >= std::max(base, 1); --k) adj_step(c, k);
+            TRY(fwd_range(c, base, base + K - 1, false, true));
+            TRY(adj_range(c, base + K - 1, std::max(base, 1)));
         }
     }
     if (!c.plan) HIP_TRY(hipGetLastError());
@@ -1043,7 +1220,9 @@ int backward_phase(Ctx &c)
 int check_level(Ctx &c, int L)
 {
     float *d = c.f_at(c.L.vstats, true);
-    launch_nonfinite_level(c.d_jobs, c.p->nshots, L, d, c.st);
+    const int slot = c.po.every == 0 && c.po.kind != FWI_CKPT_REVOLVE && c.po.tb_steps > 0
+                         ? 2 * c.fwd_pair + (L & 1) : L % c.po.R;
+    launch_nonfinite_level(c.d_jobs, c.p->nshots, slot, d, c.st);
     HIP_TRY(hipGetLastError());
     std::vector<float> h((size_t)vstats_blocks());
     HIP_TRY(hipMemcpyAsync(h.data(), d, h.size() * 4, hipMemcpyDeviceToHost, c.st));
@@ -1139,7 +1318,7 @@ int run_immediate(fwi_job *J, const JobOp &o)
         return FWI_OK;
     }
     case JOP_ZERO_ADJ:
-        zero(c.jobs[0].adj, 2 * fs, c.st);
+        zero(c.jobs[0].adj, 2 * fs, c.st);   // jobs step one level per launch
         zero(c.jobs[0].grad, fs, c.st);
         return FWI_OK;
     case JOP_FOLD: return fold(c, J->v, J->dv);
@@ -1299,13 +1478,14 @@ int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *c
     return FWI_OK;
 }
 
-int fwi_forward(const fwi_problem *prob, const float *v, const float *src,
-                const int32_t *src_pos, const int32_t *rec_pos, float *traces, void *ws,
-                uint64_t ws_bytes, void *stream)
+// tb: whether several 2-D steps may share a launch (they need more workspace)
+static int forward_call(const fwi_problem *prob, const float *v, const float *src,
+                        const int32_t *src_pos, const int32_t *rec_pos, float *traces, void *ws,
+                        uint64_t ws_bytes, void *stream, bool tb)
 {
     try {
         Ctx c;
-        int st = prepare(c, prob, FWI_MODE_FORWARD, nullptr, ws, ws_bytes, nullptr, 0, stream);
+        int st = prepare(c, prob, FWI_MODE_FORWARD, nullptr, ws, ws_bytes, nullptr, 0, stream, tb);
         if (st) return st;
         if (!src || (prob->nrec > 0 && !traces)) return fail(FWI_EINVAL, "NULL input/output array");
         st = stage(c, v, src, src_pos, rec_pos, prob->nrec > 0 ? traces : nullptr, nullptr, 0);
@@ -1320,6 +1500,13 @@ int fwi_forward(const fwi_problem *prob, const float *v, const float *src,
     }
 }
 
+int fwi_forward(const fwi_problem *prob, const float *v, const float *src,
+                const int32_t *src_pos, const int32_t *rec_pos, float *traces, void *ws,
+                uint64_t ws_bytes, void *stream)
+{
+    return forward_call(prob, v, src, src_pos, rec_pos, traces, ws, ws_bytes, stream, true);
+}
+
 int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *src,
                         const int32_t *src_pos, const int32_t *rec_pos, float *traces,
                         void *stream)
@@ -1327,6 +1514,17 @@ int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *sr
     uint64_t need = 0;
     int st = fwi_workspace_bytes(prob, FWI_MODE_FORWARD, nullptr, &need);
     if (st) return st;
+    bool tb = true;
+    if (need > kScratchBytes) {   // one 2-D step per launch needs two fields less
+        Geometry g;
+        Policy po;
+        Layout L;
+        TRY(make_geometry(prob, &g));
+        TRY(make_policy(prob, g, FWI_MODE_FORWARD, nullptr, &po, false));
+        make_layout(prob, g, po, FWI_MODE_FORWARD, &L);
+        need = L.ws_total;
+        tb = false;
+    }
     if (need > kScratchBytes)
         return fail(FWI_ENOMEM,
                     "fwi_forward_noalloc: the problem needs %llu workspace bytes, more than the "
@@ -1335,7 +1533,7 @@ int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *sr
     void *ws = nullptr;
     if (scratch_address(&ws) != 0)
         return fail(FWI_EHIP, "fwi_forward_noalloc: no address for the fixed workspace");
-    return fwi_forward(prob, v, src, src_pos, rec_pos, traces, ws, kScratchBytes, stream);
+    return forward_call(prob, v, src, src_pos, rec_pos, traces, ws, kScratchBytes, stream, tb);
 }
 
 int fwi_forward_ckpt(const fwi_problem *prob, const float *v, const float *src,
