@@ -87,6 +87,33 @@ struct Job {
     const int32_t *lev;
 };
 
+// Staging of a call on the device (k_stage_*): what the host reads back, the
+// arrays, and the distance of consecutive shots' fields.
+struct StageResult {
+    float vmin, vmax, bad_v;         // velocity range, non-finite cells
+    int32_t duplicates;              // receivers share a cell
+    int64_t bad_src, bad_rec;        // first position outside the model
+};
+struct StageArgs {
+    const float *v;
+    int64_t ncells;                  // model cells
+    float *partial;                  // [3][vblocks]
+    int32_t vblocks;
+    int32_t S, R, D, M, gy, nb, nz, nya, pitch, nzm, nym, nxm;
+    const int32_t *src_pos, *rec_pos;
+    int32_t *map;                    // scratch: a field per shot, mstride apart
+    int64_t mstride;
+    int64_t *rec_off;
+    int32_t *rec_next, *rec_head;
+    int64_t bins;                    // 2-D: list bounds per shot (column tiles x rows + 1)
+    int32_t *rt_start, *rt_rec, *rt_key;
+    int32_t *zrange;                 // [S][2] rows that hold receivers
+    StageResult *result;
+};
+struct JobStrides {
+    int64_t ring, adj, snap;
+};
+
 // Forward levels that a launch finds in the snapshot store instead of the
 // ring: level lev[i] is field fld[i] of each job's store (slot s holds fields
 // 2s and 2s+1).  Binomial checkpointing uses it to read a restored state, or

@@ -41,26 +41,31 @@ namespace fwi {
 
 // ------------------------------------------------------------ side kernels
 // kappa' = (v dt/dx)^2 on the padded grid (edge-replicated model), 0 on the frame.
-__global__ void k_prep_kappa(const float *__restrict__ v, float *__restrict__ kappa,
-                             int M, int gy, int nz, int ny, int nx, int pitch, int nya,
-                             int nb, int nzm, int nym, int nxm, int64_t total, float dt_dx)
+// One wavefront per row, so the plane, row and their clamps are found once per
+// row.
+__global__ __launch_bounds__(256) void k_prep_kappa(const float *__restrict__ v,
+                                                    float *__restrict__ kappa, int M, int gy,
+                                                    int nz, int ny, int nx, int pitch, int nya,
+                                                    int nb, int nzm, int nym, int nxm, int64_t rows,
+                                                    float dt_dx)
 {
-    const int64_t plane = (int64_t)nya * pitch;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t zi = idx / plane;
-        const int64_t rem = idx - zi * plane;
-        const int yi = (int)(rem / pitch), ci = (int)(rem % pitch);
-        const int z = (int)zi - M, y = yi - gy, x = ci - M;
-        float out = 0.f;
-        if (z >= 0 && z < nz && y >= 0 && y < ny && x >= 0 && x < nx) {
-            const int zm = min(max(z - nb, 0), nzm - 1);
-            const int ym = min(max(y - nb, 0), nym - 1);
-            const int xm = min(max(x - nb, 0), nxm - 1);
-            const float t = v[((int64_t)zm * nym + ym) * nxm + xm] * dt_dx;
-            out = t * t;
+    const int lane = threadIdx.x & 63;
+    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < rows; r += nw) {
+        const int zi = (int)(r / nya), z = zi - M, y = (int)(r - (int64_t)zi * nya) - gy;
+        const bool in = z >= 0 && z < nz && y >= 0 && y < ny;
+        const int zm = min(max(z - nb, 0), nzm - 1), ym = min(max(y - nb, 0), nym - 1);
+        const float *src = v + ((int64_t)zm * nym + ym) * nxm;
+        float *dst = kappa + r * pitch;
+        for (int c = lane; c < pitch; c += 64) {
+            const int x = c - M;
+            float out = 0.f;
+            if (in && x >= 0 && x < nx) {
+                const float t = src[min(max(x - nb, 0), nxm - 1)] * dt_dx;
+                out = t * t;
+            }
+            dst[c] = out;
         }
-        kappa[idx] = out;
     }
 }
 
@@ -259,6 +264,216 @@ __global__ __launch_bounds__(256) void k_vstats(const float *__restrict__ v, int
         partial[gridDim.x + blockIdx.x] = smax[0];
         partial[2 * gridDim.x + blockIdx.x] = sbad[0];
     }
+}
+
+// ------------------------------------------------------------ call staging
+// A call's tables are built on the device from its position arrays: copying
+// them to the host, sorting the receivers of each shot there and uploading the
+// tables took 1.9 ms of a 256^3 call with 65536 receivers, 7.6 ms of a 512 x
+// 512 x 256 one and 0.07 ms of a 128 x 128 one.  The host reads back one
+// StageResult and checks it.
+
+// Model statistics (as k_vstats), and the initial values of the kernels below.
+__global__ __launch_bounds__(256) void k_stage_begin(StageArgs a)
+{
+    const int B = a.vblocks;
+    if ((int)blockIdx.x >= B) {
+        const int64_t n = (int64_t)(gridDim.x - B) * blockDim.x;
+        const int64_t i0 = (int64_t)(blockIdx.x - B) * blockDim.x + threadIdx.x;
+        if (i0 == 0) {
+            a.result->bad_src = a.result->bad_rec = 0x7fffffffffffffffll;
+            a.result->duplicates = 0;
+        }
+        for (int64_t i = i0; i < (int64_t)a.S * a.bins; i += n) a.rt_start[i] = 0;
+        for (int64_t i = i0; i < a.S; i += n) {
+            a.zrange[2 * i] = a.nz;
+            a.zrange[2 * i + 1] = 0;
+        }
+        return;
+    }
+    __shared__ float smin[256], smax[256], sbad[256];
+    float lo = INFINITY, hi = -INFINITY, bad = 0.f;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.ncells;
+         i += (int64_t)B * blockDim.x) {
+        const float x = a.v[i];
+        if (!isfinite(x)) bad += 1.f;
+        else { lo = fminf(lo, x); hi = fmaxf(hi, x); }
+    }
+    smin[threadIdx.x] = lo; smax[threadIdx.x] = hi; sbad[threadIdx.x] = bad;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) {
+            smin[threadIdx.x] = fminf(smin[threadIdx.x], smin[threadIdx.x + s]);
+            smax[threadIdx.x] = fmaxf(smax[threadIdx.x], smax[threadIdx.x + s]);
+            sbad[threadIdx.x] += sbad[threadIdx.x + s];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        a.partial[blockIdx.x] = smin[0];
+        a.partial[B + blockIdx.x] = smax[0];
+        a.partial[2 * B + blockIdx.x] = sbad[0];
+    }
+}
+
+// Bounds of every source and receiver (the first one outside the model),
+// receiver offsets (-1: outside), and their map cells set to "no receiver".
+__global__ __launch_bounds__(256) void k_stage_positions(StageArgs a)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    auto inside = [&](const int32_t *q) {
+        const int x = q[a.D - 1], y = a.D == 3 ? q[1] : 0;
+        return q[0] >= 0 && q[0] < a.nzm && y >= 0 && y < a.nym && x >= 0 && x < a.nxm;
+    };
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + a.S;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (i >= n) {
+            if (!inside(a.src_pos + (i - n) * a.D))
+                atomicMin((unsigned long long *)&a.result->bad_src, (unsigned long long)(i - n));
+            continue;
+        }
+        const int32_t *q = a.rec_pos + i * a.D;
+        if (!inside(q)) {
+            atomicMin((unsigned long long *)&a.result->bad_rec, (unsigned long long)i);
+            a.rec_off[i] = -1;
+            continue;
+        }
+        const int z = q[0] + a.nb, y = a.D == 3 ? q[1] + a.nb : 0, x = q[a.D - 1] + a.nb;
+        const int64_t off = ((int64_t)(z + a.M) * a.nya + (y + a.gy)) * a.pitch + (x + a.M);
+        a.rec_off[i] = off;
+        a.map[i / a.R * a.mstride + off] = 0x7fffffff;
+    }
+}
+
+// The first receiver of every receiver cell.
+__global__ __launch_bounds__(256) void k_stage_first(StageArgs a)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t off = a.rec_off[i], s = i / a.R;
+        if (off >= 0) atomicMin(a.map + s * a.mstride + off, (int)(i - s * a.R));
+    }
+}
+
+// Heads, and (2-D) the receiver cells of each 64-column tile's rows; block 0
+// also reduces the model statistics.
+__global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t off = a.rec_off[i], s = i / a.R;
+        const int head = off >= 0 && a.map[s * a.mstride + off] == (int)(i - s * a.R);
+        a.rec_head[i] = head;
+        a.rec_next[i] = -1;
+        if (off >= 0 && !head) a.result->duplicates = 1;
+        if (a.bins > 0 && head) {
+            const int z = (int)(off / a.pitch) - a.M, c = (int)(off % a.pitch);
+            atomicAdd(a.rt_start + s * a.bins + (int64_t)(c / kTileX) * a.nz + z + 1, 1);
+            atomicMin(a.zrange + 2 * s, z);
+            atomicMax(a.zrange + 2 * s + 1, z + 1);
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        float lo = INFINITY, hi = -INFINITY, bad = 0.f;
+        for (int i = threadIdx.x; i < a.vblocks; i += 64) {
+            lo = fminf(lo, a.partial[i]);
+            hi = fmaxf(hi, a.partial[a.vblocks + i]);
+            bad += a.partial[2 * a.vblocks + i];
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o));
+            hi = fmaxf(hi, __shfl_xor(hi, o));
+            bad += __shfl_xor(bad, o);
+        }
+        if (threadIdx.x == 0) {
+            a.result->vmin = lo;
+            a.result->vmax = hi;
+            a.result->bad_v = bad;
+        }
+    }
+}
+
+// 2-D: exclusive prefix sums of a shot's row counts (entry t + 1 becomes the
+// start of bin t; k_stage_lists moves it to its end, the start of bin t + 1).
+__global__ __launch_bounds__(1024) void k_stage_scan(StageArgs a)
+{
+    __shared__ int wsum[16];
+    __shared__ int carry;
+    int32_t *st = a.rt_start + (int64_t)blockIdx.x * a.bins + 1;
+    const int n = (int)a.bins - 1, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += 1024) {
+        const int i = i0 + (int)threadIdx.x, c = i < n ? st[i] : 0;
+        int s = c;   // inclusive within the wave
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(s, o);
+            if (lane >= o) s += t;
+        }
+        if (lane == 63) wsum[w] = s;
+        __syncthreads();
+        int before = carry, total = 0;
+        for (int q = 0; q < 16; ++q) {
+            before += q < w ? wsum[q] : 0;
+            total += wsum[q];
+        }
+        if (i < n) st[i] = before + s - c;
+        __syncthreads();
+        if (threadIdx.x == 0) carry += total;
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void k_stage_lists(StageArgs a)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (!a.rec_head[i]) continue;
+        const int64_t off = a.rec_off[i], s = i / a.R;
+        const int z = (int)(off / a.pitch) - a.M, c = (int)(off % a.pitch);
+        // (the order within a row does not matter: its cells are distinct)
+        const int p = atomicAdd(a.rt_start + s * a.bins + (int64_t)(c / kTileX) * a.nz + z + 1, 1);
+        a.rt_rec[s * a.R + p] = (int)(i - s * a.R);
+        a.rt_key[s * a.R + p] = z << 6 | (c % kTileX);
+    }
+}
+
+// The job table from shot 0's entry: each shot's fields, tables and source.
+__global__ __launch_bounds__(64) void k_stage_jobs(StageArgs a, Job J, JobStrides d,
+                                                   Job *__restrict__ jobs, int *__restrict__ prefix)
+{
+    const int s = blockIdx.x * 64 + threadIdx.x;
+    if (s > a.S) return;
+    prefix[s] = s * J.tile[0].ntiles;
+    prefix[a.S + 1 + s] = s * J.ngather;
+    prefix[2 * (a.S + 1) + s] = s * J.tile[1].ntiles;
+    if (s == a.S) return;
+    const int64_t r = (int64_t)s * a.R;
+    J.ring += s * d.ring;
+    if (J.adj) J.adj += s * d.adj;
+    if (J.grad) J.grad += s * J.fstride;
+    if (J.snap) J.snap += s * d.snap;
+    if (J.wavelet) J.wavelet += (int64_t)s * J.nt;
+    if (J.traces) J.traces += (int64_t)s * J.nt * a.R;
+    if (J.res) J.res += (int64_t)s * J.nt * a.R;
+    J.rec_off += r;
+    J.rec_next += r;
+    J.rec_head += r;
+    if (a.bins > 0) {
+        J.rt_start += s * a.bins;
+        J.rt_rec += r;
+        J.rt_key += r;
+        J.rec_z0 = a.zrange[2 * s];
+        J.rec_z1 = a.zrange[2 * s + 1];
+    }
+    const int32_t *q = a.src_pos + (int64_t)s * a.D;
+    J.src_z = q[0] + a.nb;
+    J.src_y = a.D == 3 ? q[1] + a.nb : 0;
+    J.src_x = q[a.D - 1] + a.nb;
+    jobs[s] = J;
 }
 
 // --------------------------------------------------- bandwidth ceiling probe
@@ -712,6 +927,7 @@ int scratch_address(void **ptr)
 
 // ---------------------------------------------------------------- launchers
 int vstats_blocks() { return 256; }
+int nonfinite_blocks() { return 3 * vstats_blocks(); }   // fills the statistics' partials
 
 void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *levels,
                      hipStream_t st)
@@ -720,9 +936,33 @@ void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *le
                        prefix, levels);
 }
 
+// Everything up to the result that the host checks.
+void launch_stage_check(const StageArgs &a, hipStream_t st)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    auto blocks = [](int64_t m) { return (int)std::max<int64_t>(1, std::min<int64_t>((m + 255) / 256, 2048)); };
+    hipLaunchKernelGGL(k_stage_begin, dim3(a.vblocks + blocks((int64_t)a.S * std::max<int64_t>(a.bins, 1))),
+                       dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_stage_positions, dim3(blocks(n + a.S)), dim3(256), 0, st, a);
+    if (n > 0) hipLaunchKernelGGL(k_stage_first, dim3(blocks(n)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_stage_heads, dim3(blocks(n)), dim3(256), 0, st, a);
+}
+
+void launch_stage_tables(const StageArgs &a, const Job &j0, const JobStrides &d, Job *jobs,
+                         int *prefix, hipStream_t st)
+{
+    const int64_t n = (int64_t)a.S * a.R;
+    if (a.bins > 0 && n > 0) {
+        hipLaunchKernelGGL(k_stage_scan, dim3(a.S), dim3(1024), 0, st, a);
+        hipLaunchKernelGGL(k_stage_lists, dim3((int)std::min<int64_t>((n + 255) / 256, 2048)),
+                           dim3(256), 0, st, a);
+    }
+    hipLaunchKernelGGL(k_stage_jobs, dim3(a.S / 64 + 1), dim3(64), 0, st, a, j0, d, jobs, prefix);
+}
+
 void launch_nonfinite_level(const Job *jobs, int njobs, int slot, float *partial, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_nonfinite_level, dim3(vstats_blocks()), dim3(256), 0, st, jobs, njobs,
+    hipLaunchKernelGGL(k_nonfinite_level, dim3(nonfinite_blocks()), dim3(256), 0, st, jobs, njobs,
                        slot, partial);
 }
 
@@ -788,11 +1028,11 @@ static int grid_for(int64_t n, int threads, int cap)
 }
 
 void launch_prep_kappa(const float *v, float *kappa, int M, int gy, int nz, int ny, int nx,
-                       int pitch, int nya, int nb, int nzm, int nym, int nxm, int64_t total,
+                       int pitch, int nya, int nb, int nzm, int nym, int nxm, int64_t rows,
                        float dt_dx, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_prep_kappa, dim3(grid_for(total, 256, 65536)), dim3(256), 0, st, v,
-                       kappa, M, gy, nz, ny, nx, pitch, nya, nb, nzm, nym, nxm, total, dt_dx);
+    hipLaunchKernelGGL(k_prep_kappa, dim3(grid_for(rows * 64, 256, 16384)), dim3(256), 0, st, v,
+                       kappa, M, gy, nz, ny, nx, pitch, nya, nb, nzm, nym, nxm, rows, dt_dx);
 }
 
 // Zero the frame and row padding of nf consecutive fields (fstride floats

@@ -28,8 +28,12 @@ void launch_step(int ndim, int M, int nw, bool adj, const Job *jobs, const int *
                  int njobs, int step, int ttiles, int gblocks, int remap, const LevelMap &lm,
                  hipStream_t st);
 void launch_prep_kappa(const float *v, float *kappa, int M, int gy, int nz, int ny, int nx,
-                       int pitch, int nya, int nb, int nzm, int nym, int nxm, int64_t total,
+                       int pitch, int nya, int nb, int nzm, int nym, int nxm, int64_t rows,
                        float dt_dx, hipStream_t st);
+void launch_stage_check(const StageArgs &a, hipStream_t st);
+void launch_stage_tables(const StageArgs &a, const Job &j0, const JobStrides &d, Job *jobs,
+                         int *prefix, hipStream_t st);
+int nonfinite_blocks();
 void launch_fill(float *p, int64_t n, float val, hipStream_t st);
 void launch_zero_frames(float *p, int64_t nfields, int64_t fstride, int nya, int pitch, int M,
                         int gy, int nz, int ny, int nx, hipStream_t st);
@@ -277,7 +281,7 @@ uint64_t max_adj_tiles_2d(const Geometry &g)
 struct Layout {
     uint64_t kappa = 0, ring = 0, adj = 0, grad = 0, snap = 0;
     uint64_t jobs = 0, prefix = 0, rec_off = 0, rec_next = 0, rec_head = 0, rt_start = 0, rt_rec = 0;
-    uint64_t rt_key = 0;
+    uint64_t rt_key = 0, zrange = 0, stage = 0;
     uint64_t res = 0, partial = 0, misfit = 0, fold1 = 0, fold2 = 0, vstats = 0;
     bool ring_in_ws = false, has_adj = false, has_res = false, has_fold = false;
     uint64_t ws_total = 0, ck_total = 0;
@@ -311,6 +315,8 @@ void make_layout(const fwi_problem *p, const Geometry &g, const Policy &po, int 
         L->rt_rec = w.take(sizeof(int32_t) * S * R + 4);
         L->rt_key = w.take(sizeof(int32_t) * S * R + 4);
     }
+    L->zrange = w.take(sizeof(int32_t) * 2 * S);
+    L->stage = w.take(sizeof(StageResult));
     L->vstats = w.take(sizeof(float) * 3ull * vstats_blocks());
     if (mode == FWI_MODE_BACKWARD || mode == FWI_MODE_GRADIENT) {
         L->has_adj = true;
@@ -605,8 +611,31 @@ int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws
     return FWI_OK;
 }
 
-// Reads positions and model statistics back, checks them, and uploads the
-// job table.  res: adjoint source (or NULL); traces: recording target (or NULL).
+// Receivers that share a cell: each one's next receiver on the cell, in index
+// order (rec_next; the first of a cell is its head).  Sorted on the host, since
+// only calls with such receivers need it.
+int stage_duplicates(Ctx &c, const StageArgs &a)
+{
+    const size_t S = (size_t)a.S, R = (size_t)a.R;
+    std::vector<int64_t> roff(S * R);
+    HIP_TRY(hipMemcpyAsync(roff.data(), a.rec_off, roff.size() * 8, hipMemcpyDeviceToHost, c.st));
+    HIP_TRY(hipStreamSynchronize(c.st));
+    std::vector<int32_t> rnext(S * R, -1), order(R);
+    for (size_t s = 0; s < S; ++s) {
+        const int64_t *o = roff.data() + s * R;
+        for (size_t r = 0; r < R; ++r) order[r] = (int32_t)r;
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return o[x] < o[y]; });
+        for (size_t i = 0; i + 1 < R; ++i)
+            if (o[order[i + 1]] == o[order[i]]) rnext[s * R + order[i]] = order[i + 1];
+    }
+    HIP_TRY(hipMemcpyAsync(a.rec_next, rnext.data(), rnext.size() * 4, hipMemcpyHostToDevice, c.st));
+    HIP_TRY(hipStreamSynchronize(c.st));   // rnext dies with this frame
+    return FWI_OK;
+}
+
+// Builds the call's tables on the device, reads back what has to be checked
+// (the call's one synchronisation at its start) and starts kappa'.  res:
+// adjoint source (or NULL); traces: recording target (or NULL).
 int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
           const int32_t *rec_pos, float *traces, const float *res, int accumulate)
 {
@@ -614,36 +643,49 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     const Geometry &g = c.g;
     const int S = p->nshots, R = p->nrec, D = p->ndim;
     if (!v || !src_pos || (R > 0 && !rec_pos)) return fail(FWI_EINVAL, "NULL input array");
-    std::vector<int32_t> hs((size_t)S * D), hr((size_t)S * R * D);
-    HIP_TRY(hipMemcpyAsync(hs.data(), src_pos, hs.size() * 4, hipMemcpyDeviceToHost, c.st));
-    if (!hr.empty())
-        HIP_TRY(hipMemcpyAsync(hr.data(), rec_pos, hr.size() * 4, hipMemcpyDeviceToHost, c.st));
-    float *d_vs = c.f_at(c.L.vstats, true);
-    launch_vstats(v, g.model_cells, d_vs, c.st);
+    const uint64_t fs = (uint64_t)g.fstride;
+    float *ring = c.f_at(c.L.ring, c.L.ring_in_ws);
+    float *snap = c.f_at(c.L.snap, c.L.ring_in_ws);
+    float *adj = c.L.has_adj ? c.f_at(c.L.adj, true) : nullptr;
+    float *grad = c.L.has_adj ? c.f_at(c.L.grad, true) : nullptr;
+    const int adj_fields = c.po.adj_steps > 0 ? 4 : 2;
+    StageArgs a{};
+    a.v = v;
+    a.ncells = g.model_cells;
+    a.partial = c.f_at(c.L.vstats, true);
+    a.vblocks = vstats_blocks();
+    a.S = S; a.R = R; a.D = D; a.M = g.M; a.gy = g.gy; a.nb = g.nb;
+    a.nz = g.nz; a.nya = g.nya; a.pitch = g.pitch;
+    a.nzm = g.nzm; a.nym = g.nym; a.nxm = g.nxm;
+    a.src_pos = src_pos;
+    a.rec_pos = rec_pos;
+    // the map's cells are scratch in a field that is cleared before it is used:
+    // an adjoint field, or (forward calls) the ring's level 0
+    a.map = reinterpret_cast<int32_t *>(adj ? adj : ring);
+    a.mstride = (int64_t)(fs * (adj ? adj_fields : c.po.R));
+    a.rec_off = reinterpret_cast<int64_t *>(c.ws + c.L.rec_off);
+    a.rec_next = reinterpret_cast<int32_t *>(c.ws + c.L.rec_next);
+    a.rec_head = reinterpret_cast<int32_t *>(c.ws + c.L.rec_head);
+    if (D == 2) {
+        a.bins = (int64_t)max_adj_tiles_2d(g) + 1;
+        a.rt_start = reinterpret_cast<int32_t *>(c.ws + c.L.rt_start);
+        a.rt_rec = reinterpret_cast<int32_t *>(c.ws + c.L.rt_rec);
+        a.rt_key = reinterpret_cast<int32_t *>(c.ws + c.L.rt_key);
+    }
+    a.zrange = reinterpret_cast<int32_t *>(c.ws + c.L.zrange);
+    a.result = reinterpret_cast<StageResult *>(c.ws + c.L.stage);
+    launch_stage_check(a, c.st);
     HIP_TRY(hipGetLastError());
-    std::vector<float> hv(3 * (size_t)vstats_blocks());
-    HIP_TRY(hipMemcpyAsync(hv.data(), d_vs, hv.size() * 4, hipMemcpyDeviceToHost, c.st));
+    StageResult h{};
+    HIP_TRY(hipMemcpyAsync(&h, a.result, sizeof h, hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
 
-    const int dims[3] = {g.nzm, g.nym, g.nxm};
-    auto in_model = [&](const int32_t *q) {
-        if (D == 2) return q[0] >= 0 && q[0] < dims[0] && q[1] >= 0 && q[1] < dims[2];
-        return q[0] >= 0 && q[0] < dims[0] && q[1] >= 0 && q[1] < dims[1] && q[2] >= 0 &&
-               q[2] < dims[2];
-    };
-    for (int s = 0; s < S; ++s)
-        if (!in_model(&hs[(size_t)s * D])) return fail(FWI_EBOUNDS, "source %d outside the model", s);
-    for (size_t r = 0; r < (size_t)S * R; ++r)
-        if (!in_model(&hr[r * D])) return fail(FWI_EBOUNDS, "receiver %zu outside the model", r);
-
-    const int B = vstats_blocks();
-    float vmin = INFINITY, vmax = -INFINITY, bad = 0.f;
-    for (int i = 0; i < B; ++i) {
-        vmin = std::min(vmin, hv[i]);
-        vmax = std::max(vmax, hv[B + i]);
-        bad += hv[2 * B + i];
-    }
-    if (bad > 0.f) return fail(FWI_EINVAL, "velocity has non-finite values");
+    if (h.bad_src != INT64_MAX)
+        return fail(FWI_EBOUNDS, "source %lld outside the model", (long long)h.bad_src);
+    if (h.bad_rec != INT64_MAX)
+        return fail(FWI_EBOUNDS, "receiver %lld outside the model", (long long)h.bad_rec);
+    const float vmin = h.vmin, vmax = h.vmax;
+    if (h.bad_v > 0.f) return fail(FWI_EINVAL, "velocity has non-finite values");
     if (!(vmin > 0.f)) return fail(FWI_EINVAL, "velocity must be > 0 (min %g)", (double)vmin);
     const double cfl = (double)vmax * p->dt / p->dx;
     const double lim = std::sqrt(4.0 / (p->ndim * max_symbol(p->order)));
@@ -651,158 +693,65 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     // sponge strength: as given, or (eta_max < 0) the default for this model
     const double eta_max = p->eta_max >= 0.f ? (double)p->eta_max
                                              : default_eta_max(vmax, g.nb, p->dx);
-
-    // receiver offsets and duplicate chains (receivers sharing a cell)
-    auto offset = [&](const int32_t *q) -> int64_t {
-        const int z = q[0] + g.nb;
-        const int y = D == 3 ? q[1] + g.nb : 0;
-        const int x = (D == 3 ? q[2] : q[1]) + g.nb;
-        return ((int64_t)(z + g.M) * g.nya + (y + g.gy)) * g.pitch + (x + g.M);
-    };
-    std::vector<int64_t> roff((size_t)S * R);
-    std::vector<int32_t> rnext((size_t)S * R, -1), rhead((size_t)S * R, 0);
-    std::vector<int32_t> order(R);
-    for (int s = 0; s < S; ++s) {
-        int64_t *o = roff.data() + (size_t)s * R;
-        for (int r = 0; r < R; ++r) o[r] = offset(&hr[((size_t)s * R + r) * D]);
-        for (int r = 0; r < R; ++r) order[r] = r;
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return o[a] < o[b]; });
-        for (int i = 0; i < R; ++i) {
-            const int r = order[i];
-            const bool first = i == 0 || o[order[i - 1]] != o[r];
-            rhead[(size_t)s * R + r] = first ? 1 : 0;
-            if (i + 1 < R && o[order[i + 1]] == o[r]) rnext[(size_t)s * R + r] = order[i + 1];
-        }
+    if (h.duplicates) {
+        const int st = stage_duplicates(c, a);
+        if (st) return st;
     }
 
-    // job table: one job per shot
-    Job::Tiling til[2];
-    for (int a = 0; a < 2; ++a) {
-        tiles_for(g, S, a == 1, &til[a].ntx, &til[a].nty, &til[a].nzc, &til[a].zc);
-        til[a].ntiles = til[a].ntx * til[a].nty * til[a].nzc;
-        til[a].flags = tile_flags(g);
-    }
+    // job table: one job per shot, from the first one's entry
     c.gthreads = gather_threads(g);
-    const int ng = (R + c.gthreads - 1) / c.gthreads;
-    const uint64_t fs = (uint64_t)g.fstride;
-    float *kappa = c.f_at(c.L.kappa, true);
-    float *ring = c.f_at(c.L.ring, c.L.ring_in_ws);
-    float *snap = c.f_at(c.L.snap, c.L.ring_in_ws);
-    float *adj = c.L.has_adj ? c.f_at(c.L.adj, true) : nullptr;
-    float *grad = c.L.has_adj ? c.f_at(c.L.grad, true) : nullptr;
-    int64_t *d_roff = reinterpret_cast<int64_t *>(c.ws + c.L.rec_off);
-    int32_t *d_rnext = reinterpret_cast<int32_t *>(c.ws + c.L.rec_next);
-    int32_t *d_rhead = reinterpret_cast<int32_t *>(c.ws + c.L.rec_head);
-    // 2-D receiver lists: each receiver cell (its first receiver), sorted by
-    // 64-column tile and row
-    const bool lists = D == 2;
-    const uint64_t mt = lists ? max_adj_tiles_2d(g) + 1 : 0;
-    int32_t *d_rtstart = lists ? reinterpret_cast<int32_t *>(c.ws + c.L.rt_start) : nullptr;
-    int32_t *d_rtrec = lists ? reinterpret_cast<int32_t *>(c.ws + c.L.rt_rec) : nullptr;
-    int32_t *d_rtkey = lists ? reinterpret_cast<int32_t *>(c.ws + c.L.rt_key) : nullptr;
-    std::vector<int32_t> rtstart((size_t)S * mt, 0), rtrec(lists ? (size_t)S * R : 0);
-    std::vector<int32_t> rtkey(rtrec.size());
-    std::vector<int32_t> rz0(S, g.nz), rz1(S, 0);   // rows that hold receivers
-    if (lists) {
-        std::vector<std::pair<int64_t, int32_t>> key;
-        for (int s = 0; s < S; ++s) {
-            key.clear();
-            for (int r = 0; r < R; ++r) {
-                if (!rhead[(size_t)s * R + r]) continue;
-                const int64_t off = roff[(size_t)s * R + r];
-                const int zr = (int)(off / g.pitch) - g.M, cr = (int)(off % g.pitch);
-                rz0[s] = std::min(rz0[s], zr);
-                rz1[s] = std::max(rz1[s], zr + 1);
-                key.push_back({((int64_t)(cr / kTileX) * g.nz + zr) * kTileX + cr % kTileX, r});
-            }
-            std::sort(key.begin(), key.end());   // one entry per cell: keys differ
-            int32_t *st = &rtstart[(size_t)s * mt];
-            int32_t *lst = &rtrec[(size_t)s * R];
-            int32_t *kk = &rtkey[(size_t)s * R];
-            for (size_t i = 0; i < key.size(); ++i) {
-                const int64_t tz = key[i].first / kTileX;   // tile * nz + row
-                lst[i] = key[i].second;
-                kk[i] = (int32_t)((tz % g.nz) << 6 | (key[i].first % kTileX));
-                st[tz + 1] += 1;
-            }
-            for (uint64_t t = 1; t < mt; ++t) st[t] += st[t - 1];
-        }
-    }
     double cell = 1.0;
-    for (int a = 0; a < D; ++a) cell *= p->dx;
-    c.jobs.assign(S, Job{});
-    // [forward tile prefix | gather prefix | adjoint tile prefix], S+1 each
-    std::vector<int> prefix(3 * (S + 1), 0);
-    for (int s = 0; s < S; ++s) {
-        Job &J = c.jobs[s];
-        J.nz = g.nz; J.ny = g.ny; J.nx = g.nx;
-        J.pitch = g.pitch; J.nya = g.nya; J.nb = g.nb;
-        J.plane = g.plane; J.fstride = g.fstride;
-        J.eta_dt = g.nb > 0 ? (float)(eta_max * p->dt / ((double)g.nb * g.nb)) : 0.f;
-        J.src_scale = (float)((double)p->dt * p->dt / cell);
-        J.tile[0] = til[0];
-        J.tile[1] = til[1];
-        J.ngather = ng;
-        J.n0 = 0; J.k0 = 0; J.nt = p->nt;
-        J.fwd_lo = 0; J.fwd_hi = p->nt;
-        J.adj_lo = 1; J.adj_hi = p->nt + 1;
-        J.record = traces != nullptr;
-        J.accumulate = accumulate;
-        J.kappa = kappa;
-        J.ring = ring + (uint64_t)s * c.po.R * fs;
-        J.R = c.po.R;
-        J.adj = adj ? adj + (uint64_t)s * (c.po.adj_steps > 0 ? 4 : 2) * fs : nullptr;
-        J.grad = grad ? grad + (uint64_t)s * fs : nullptr;
-        J.snap = c.po.nsnap > 0 ? snap + (uint64_t)s * 2 * c.po.nsnap * fs : nullptr;
-        const int32_t *q = &hs[(size_t)s * D];
-        J.src_z = q[0] + g.nb;
-        J.src_y = D == 3 ? q[1] + g.nb : 0;
-        J.src_x = (D == 3 ? q[2] : q[1]) + g.nb;
-        J.nrec = R;
-        J.wavelet = src ? src + (size_t)s * p->nt : nullptr;
-        J.rec_off = d_roff + (size_t)s * R;
-        J.rec_next = d_rnext + (size_t)s * R;
-        J.rec_head = d_rhead + (size_t)s * R;
-        J.rec_z0 = lists ? rz0[s] : 0;
-        J.rec_z1 = lists ? rz1[s] : 0;
-        J.rt_start = lists ? d_rtstart + (size_t)s * mt : nullptr;
-        J.rt_rec = lists ? d_rtrec + (size_t)s * R : nullptr;
-        J.rt_key = lists ? d_rtkey + (size_t)s * R : nullptr;
-        J.traces = traces ? traces + (size_t)s * p->nt * R : nullptr;
-        J.res = res ? res + (size_t)s * p->nt * R : nullptr;
-        prefix[s + 1] = prefix[s] + J.tile[0].ntiles;
-        prefix[S + 1 + s + 1] = prefix[S + 1 + s] + ng;
-        prefix[2 * (S + 1) + s + 1] = prefix[2 * (S + 1) + s] + J.tile[1].ntiles;
+    for (int i = 0; i < D; ++i) cell *= p->dx;
+    c.jobs.assign(1, Job{});
+    Job &J = c.jobs[0];
+    for (int i = 0; i < 2; ++i) {
+        tiles_for(g, S, i == 1, &J.tile[i].ntx, &J.tile[i].nty, &J.tile[i].nzc, &J.tile[i].zc);
+        J.tile[i].ntiles = J.tile[i].ntx * J.tile[i].nty * J.tile[i].nzc;
+        J.tile[i].flags = tile_flags(g);
     }
-    c.ttiles = prefix[S];
-    c.gblocks = prefix[2 * S + 1];
-    c.atiles = prefix[3 * S + 2];
+    J.ngather = (R + c.gthreads - 1) / c.gthreads;
+    J.nz = g.nz; J.ny = g.ny; J.nx = g.nx;
+    J.pitch = g.pitch; J.nya = g.nya; J.nb = g.nb;
+    J.plane = g.plane; J.fstride = g.fstride;
+    J.eta_dt = g.nb > 0 ? (float)(eta_max * p->dt / ((double)g.nb * g.nb)) : 0.f;
+    J.src_scale = (float)((double)p->dt * p->dt / cell);
+    J.n0 = 0; J.k0 = 0; J.nt = p->nt;
+    J.fwd_lo = 0; J.fwd_hi = p->nt;
+    J.adj_lo = 1; J.adj_hi = p->nt + 1;
+    J.record = traces != nullptr;
+    J.accumulate = accumulate;
+    float *kappa = c.f_at(c.L.kappa, true);
+    J.kappa = kappa;
+    J.ring = ring;
+    J.R = c.po.R;
+    J.adj = adj;
+    J.grad = grad;
+    J.snap = c.po.nsnap > 0 ? snap : nullptr;
+    J.nrec = R;
+    J.wavelet = src;
+    J.rec_off = a.rec_off;
+    J.rec_next = a.rec_next;
+    J.rec_head = a.rec_head;
+    J.rt_start = a.rt_start;
+    J.rt_rec = a.rt_rec;
+    J.rt_key = a.rt_key;
+    J.traces = traces;
+    J.res = res;
+    JobStrides d{};
+    d.ring = (int64_t)fs * c.po.R;
+    d.adj = (int64_t)fs * adj_fields;
+    d.snap = (int64_t)fs * 2 * c.po.nsnap;
+    c.ttiles = S * J.tile[0].ntiles;
+    c.gblocks = S * J.ngather;
+    c.atiles = S * J.tile[1].ntiles;
     c.d_jobs = reinterpret_cast<Job *>(c.ws + c.L.jobs);
+    // [forward tile prefix | gather prefix | adjoint tile prefix], S+1 each
     c.d_prefix = reinterpret_cast<int *>(c.ws + c.L.prefix);
-    HIP_TRY(hipMemcpyAsync(c.d_jobs, c.jobs.data(), sizeof(Job) * S, hipMemcpyHostToDevice, c.st));
-    HIP_TRY(hipMemcpyAsync(c.d_prefix, prefix.data(), sizeof(int) * prefix.size(),
-                           hipMemcpyHostToDevice, c.st));
-    if (lists) {
-        HIP_TRY(hipMemcpyAsync(d_rtstart, rtstart.data(), rtstart.size() * 4,
-                               hipMemcpyHostToDevice, c.st));
-        if (R > 0) {
-            HIP_TRY(hipMemcpyAsync(d_rtrec, rtrec.data(), rtrec.size() * 4,
-                                   hipMemcpyHostToDevice, c.st));
-            HIP_TRY(hipMemcpyAsync(d_rtkey, rtkey.data(), rtkey.size() * 4,
-                                   hipMemcpyHostToDevice, c.st));
-        }
-    }
-    if (R > 0) {
-        HIP_TRY(hipMemcpyAsync(d_roff, roff.data(), roff.size() * 8, hipMemcpyHostToDevice, c.st));
-        HIP_TRY(hipMemcpyAsync(d_rnext, rnext.data(), rnext.size() * 4, hipMemcpyHostToDevice, c.st));
-        HIP_TRY(hipMemcpyAsync(d_rhead, rhead.data(), rhead.size() * 4, hipMemcpyHostToDevice, c.st));
-    }
+    launch_stage_tables(a, J, d, c.d_jobs, c.d_prefix, c.st);
     // model -> kappa' = (v dt/dx)^2 on the padded grid
     launch_prep_kappa(v, kappa, g.M, g.gy, g.nz, g.ny, g.nx, g.pitch, g.nya, g.nb, g.nzm, g.nym,
-                      g.nxm, g.fstride, (float)((double)p->dt / p->dx), c.st);
+                      g.nxm, g.fstride / g.pitch, (float)((double)p->dt / p->dx), c.st);
     HIP_TRY(hipGetLastError());
-    // host staging vectors die with this frame: finish the uploads now
-    HIP_TRY(hipStreamSynchronize(c.st));
     return FWI_OK;
 }
 
@@ -1094,7 +1043,6 @@ void zero_frames(const Ctx &c, float *p, uint64_t nf)
 int forward_phase(Ctx &c, bool record)
 {
     const int nt = c.p->nt;
-    const uint64_t fs = (uint64_t)c.g.fstride;
     if (!c.plan) {
         zero_frames(c, c.jobs[0].ring, (uint64_t)c.po.R * c.p->nshots);
         // levels 0 and -1: the zero initial state (FORWARD mode on pairs of
@@ -1224,7 +1172,7 @@ int check_level(Ctx &c, int L)
                          ? 2 * c.fwd_pair + (L & 1) : L % c.po.R;
     launch_nonfinite_level(c.d_jobs, c.p->nshots, slot, d, c.st);
     HIP_TRY(hipGetLastError());
-    std::vector<float> h((size_t)vstats_blocks());
+    std::vector<float> h((size_t)nonfinite_blocks());
     HIP_TRY(hipMemcpyAsync(h.data(), d, h.size() * 4, hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
     float bad = 0.f;
@@ -1806,6 +1754,8 @@ int fwi_job_create(const fwi_problem *prob, int32_t kind, int32_t chunk, const f
         st = stage(c, v, src, src_pos, rec_pos, rec ? J->rec : nullptr, J->res,
                    kind == FWI_JOB_GRADIENT);
         if (st) return st;
+        // the job may be advanced on another stream, and its inputs released
+        HIP_TRY(hipStreamSynchronize(c.st));
         // frames of every level; levels 0 and -1 whole (the job's program
         // also clears them before its first step)
         zero_frames(c, c.jobs[0].ring, (uint64_t)c.po.R);
