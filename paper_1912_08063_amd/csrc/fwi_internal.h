@@ -17,8 +17,6 @@
 namespace fwi {
 
 constexpr int kTileX = 64;   // memory columns per tile (one wavefront)
-// 3-D blocks hold 4 or 8 wavefronts of 64 lanes, each thread owning 2 or 4
-// consecutive y rows: a tile is 64 (x) by rows * wavefronts (y)
 constexpr int kGatherThreads = 256;
 // Tiling flags of 3-D step launches.  kTileZFast: the z chunk is the fastest
 // index of a tile number (the chunks of one column are consecutive blocks),
@@ -28,6 +26,13 @@ constexpr int kGatherThreads = 256;
 // both, instead of once at the start and once at the end.
 constexpr int32_t kTileZFast = 1;
 constexpr int32_t kTileZAlt = 2;
+
+// 3-D steps without marching (k_step3d_tile) or marching (k_step3d): kernel code,
+// tile rows, and the planes of a tile without marching.
+// Receiver lists of 3-D jobs are by 64 columns x kTile3dRows rows x 1 plane, their
+// keys plane << kKeyBits3d | row << 6 | column.
+constexpr int kTile3dCode = 3, kMarch3dCode = 4, kTile3dRows = 16, kTile3dPlanes = 4, kTile3dThreads = 256;
+constexpr int kKeyBits3d = 10;
 
 // Size of the fixed per-GPU workspace of fwi_forward_noalloc.
 constexpr uint64_t kScratchBytes = 128ull << 20;
@@ -73,12 +78,12 @@ struct Job {
     const int64_t *rec_off;    // [nrec] field offsets of the receiver cells
     const int32_t *rec_next;   // [nrec] next receiver on the same cell, -1 at the end
     const int32_t *rec_head;   // [nrec] 1 for the first receiver of its cell
-    // 2-D receiver lists: the first receiver of each receiver cell, sorted by
-    // 64-column tile and row; rows z0 .. z1-1 of column tile t own entries
-    // rt_start[t nz + z0] .. rt_start[t nz + z1] - 1 of rt_rec (receiver) and
-    // rt_key (row << 6 | column within the tile)
-    int32_t rec_z0, rec_z1;    // padded rows that hold receivers (2-D): [rec_z0, rec_z1)
-    const int32_t *rt_start;   // [column tiles * nz + 1] (2-D jobs only)
+    // receiver lists: the first receiver of each receiver cell, sorted by tile
+    // (64 columns; 3-D: x kTile3dRows rows) and z; rows (planes) z0 .. z1-1 of tile
+    // t own entries rt_start[t nz + z0] .. rt_start[t nz + z1] - 1 of rt_rec
+    // (receiver) and rt_key (2-D: z << 6 | column within the tile)
+    int32_t rec_z0, rec_z1;    // padded z that hold receivers: [rec_z0, rec_z1)
+    const int32_t *rt_start;   // [tiles * nz + 1] (2-D, and 3-D jobs with an adjoint)
     const int32_t *rt_rec;     // [receiver cells]
     const int32_t *rt_key;     // [receiver cells]
     float *traces;         // [nt][nrec]
@@ -105,9 +110,10 @@ struct StageArgs {
     int64_t mstride;
     int64_t *rec_off;
     int32_t *rec_next, *rec_head;
-    int64_t bins;                    // 2-D: list bounds per shot (column tiles x rows + 1)
+    int64_t bins;                    // list bounds per shot (tiles x nz + 1; 0: no lists)
+    int32_t nty;                     // tiles in y (2-D: 1)
     int32_t *rt_start, *rt_rec, *rt_key;
-    int32_t *zrange;                 // [S][2] rows that hold receivers
+    int32_t *zrange;                 // [S][2] z that hold receivers
     StageResult *result;
 };
 struct JobStrides {

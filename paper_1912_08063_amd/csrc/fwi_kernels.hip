@@ -9,21 +9,19 @@
 // the scaled adjoint field psi' (psi = kappa*alpha*lambda, divided by dx^2),
 // for which the discrete adjoint recurrence IS the forward recurrence, and
 // accumulates the imaging condition g += psi'^{k+1} * L'p^k.  The adjoint
-// source enters at the receiver cells: inside the step in 2-D, by a launch
-// after each step in 3-D.
+// source enters at the receiver cells, inside the step.
 //
 // Design for CDNA4 (the paper's MXU band-matrix formulation does not apply:
 // the star stencil is banded, not a dense contraction, and the step is HBM
 // bound at 16 algorithmic bytes per cell-update):
-//  * 3-D: 256-thread blocks own a 64 (x) x 16 (y) column of the grid (64 x 8
-//    at 16th order and in the adjoint) over a chunk of z planes.  Each thread
-//    keeps a register queue of 2M+1 planes for the z-derivative (z marching),
-//    the current xy plane with its M-cell halo is staged in LDS for the x and
-//    y derivatives, and each thread owns 4 (or 2) consecutive y rows so
-//    y-neighbours are reused from LDS.
+//  * 3-D: 256-thread blocks own a 64 (x) x 16 (y) column of the grid over a
+//    chunk of z planes.  Each thread keeps a register queue of 2M+2 planes of
+//    four columns for the z-derivative (z marching), and the current xy plane
+//    with its M-cell halo is staged in LDS for the x and y derivatives.  Small
+//    grids take blocks of 64 x 16 x 4 cells instead (fwi_step3d.hip).
 //  * 2-D: one wavefront per block, 64 columns marching down a chunk of rows;
 //    runs of consecutive steps take several steps per launch (fwi_step2d.hip).
-//  * Each wavefront reads and writes whole aligned 256-byte row segments.
+//  * Wavefronts read and write whole aligned 256-byte row segments.
 //  * Blocks are remapped so that each XCD (one L2 each) gets a contiguous
 //    range of tiles: neighbouring tiles share their halos in the same L2.
 //  * Receiver sampling of level n is done by extra blocks of the launch that
@@ -107,22 +105,6 @@ __global__ void k_gather(const Job *__restrict__ jobs, const int *__restrict__ g
     const int j = find_job(gprefix, njobs, blockIdx.x);
     const Job *J = jobs + j;
     gather_block(J, lm, (blockIdx.x - gprefix[j]) * blockDim.x + threadIdx.x, J->n0 + step);
-}
-
-// Adjoint source of 3-D steps, a launch after each adjoint step: psi'^k[rec]
-// += kappa'[rec] * res[k-1][rec] (2-D steps add it themselves).
-__global__ void k_adj_inject(const Job *__restrict__ jobs, const int *__restrict__ gprefix,
-                             int njobs, int step)
-{
-    const int j = find_job(gprefix, njobs, blockIdx.x);
-    const Job *J = jobs + j;
-    const int k = step_level(J, step, true);
-    const int r = (blockIdx.x - gprefix[j]) * blockDim.x + threadIdx.x;
-    if (k < J->adj_lo || k >= J->adj_hi || r >= J->nrec || !J->rec_head[r]) return;
-    const float s = adj_source(J, k, r);
-    const int64_t off = J->rec_off[r];
-    float *psi = J->adj + (int64_t)(k & 1) * J->fstride;
-    psi[off] += J->kappa[off] * s;
 }
 
 // Misfit (Eq. 1) and adjoint source: res = 2 (d - obs); per-block partial sums
@@ -356,7 +338,19 @@ __global__ __launch_bounds__(256) void k_stage_first(StageArgs a)
     }
 }
 
-// Heads, and (2-D) the receiver cells of each 64-column tile's rows; block 0
+// List bin, z and key of the receiver cell at a field offset.
+__device__ __forceinline__ int64_t list_bin(const StageArgs &a, int64_t off, int &z, int &key)
+{
+    const int64_t row = off / a.pitch;
+    const int c = (int)(off - row * a.pitch), zi = (int)(row / a.nya);
+    const int y = (int)(row - (int64_t)zi * a.nya) - a.gy;
+    z = zi - a.M;
+    key = a.D == 2 ? z << 6 | (c % kTileX)
+                   : z << kKeyBits3d | (y % kTile3dRows) << 6 | (c % kTileX);
+    return ((int64_t)(c / kTileX) * a.nty + (a.D == 2 ? 0 : y / kTile3dRows)) * a.nz + z;
+}
+
+// Heads, and the receiver cells of each list bin; block 0
 // also reduces the model statistics.
 __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
 {
@@ -369,10 +363,13 @@ __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
         a.rec_next[i] = -1;
         if (off >= 0 && !head) a.result->duplicates = 1;
         if (a.bins > 0 && head) {
-            const int z = (int)(off / a.pitch) - a.M, c = (int)(off % a.pitch);
-            atomicAdd(a.rt_start + s * a.bins + (int64_t)(c / kTileX) * a.nz + z + 1, 1);
-            atomicMin(a.zrange + 2 * s, z);
-            atomicMax(a.zrange + 2 * s + 1, z + 1);
+            int z, key;
+            atomicAdd(a.rt_start + s * a.bins + list_bin(a, off, z, key) + 1, 1);
+            // (most receivers do not widen the range; a bound read too early only
+            // costs an atomic that changes nothing)
+            int32_t *zr = a.zrange + 2 * s;
+            if (z < zr[0]) atomicMin(zr, z);
+            if (z + 1 > zr[1]) atomicMax(zr + 1, z + 1);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < 64) {
@@ -395,34 +392,32 @@ __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
     }
 }
 
-// 2-D: exclusive prefix sums of a shot's row counts (entry t + 1 becomes the
+// Exclusive prefix sums of a shot's bin counts (entry t + 1 becomes the
 // start of bin t; k_stage_lists moves it to its end, the start of bin t + 1).
 __global__ __launch_bounds__(1024) void k_stage_scan(StageArgs a)
 {
     __shared__ int wsum[16];
-    __shared__ int carry;
     int32_t *st = a.rt_start + (int64_t)blockIdx.x * a.bins + 1;
     const int n = (int)a.bins - 1, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (threadIdx.x == 0) carry = 0;
+    // a run of bins per thread: their sum, the sums before it, then the bins
+    const int per = (n + 1023) / 1024, i0 = min((int)threadIdx.x * per, n), i1 = min(i0 + per, n);
+    int c = 0;
+#pragma unroll 8
+    for (int i = i0; i < i1; ++i) c += st[i];
+    int s = c;   // inclusive within the wave
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(s, o);
+        if (lane >= o) s += t;
+    }
+    if (lane == 63) wsum[w] = s;
     __syncthreads();
-    for (int i0 = 0; i0 < n; i0 += 1024) {
-        const int i = i0 + (int)threadIdx.x, c = i < n ? st[i] : 0;
-        int s = c;   // inclusive within the wave
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(s, o);
-            if (lane >= o) s += t;
-        }
-        if (lane == 63) wsum[w] = s;
-        __syncthreads();
-        int before = carry, total = 0;
-        for (int q = 0; q < 16; ++q) {
-            before += q < w ? wsum[q] : 0;
-            total += wsum[q];
-        }
-        if (i < n) st[i] = before + s - c;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += total;
-        __syncthreads();
+    int before = s - c;
+    for (int q = 0; q < w; ++q) before += wsum[q];
+#pragma unroll 8
+    for (int i = i0; i < i1; ++i) {
+        const int x = st[i];
+        st[i] = before;
+        before += x;
     }
 }
 
@@ -432,12 +427,12 @@ __global__ __launch_bounds__(256) void k_stage_lists(StageArgs a)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         if (!a.rec_head[i]) continue;
-        const int64_t off = a.rec_off[i], s = i / a.R;
-        const int z = (int)(off / a.pitch) - a.M, c = (int)(off % a.pitch);
-        // (the order within a row does not matter: its cells are distinct)
-        const int p = atomicAdd(a.rt_start + s * a.bins + (int64_t)(c / kTileX) * a.nz + z + 1, 1);
+        const int64_t s = i / a.R;
+        int z, key;
+        // (the order within a bin does not matter: its cells are distinct)
+        const int p = atomicAdd(a.rt_start + s * a.bins + list_bin(a, a.rec_off[i], z, key) + 1, 1);
         a.rt_rec[s * a.R + p] = (int)(i - s * a.R);
-        a.rt_key[s * a.R + p] = z << 6 | (c % kTileX);
+        a.rt_key[s * a.R + p] = key;
     }
 }
 
@@ -976,8 +971,7 @@ void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st)
 #define FWI_STEP3D_DECL(m)                                                                       \
     void launch_step3d_m##m(int nw, bool adj, const Job *jobs, const int *prefix, int njobs,     \
                             int step, int ttiles, int grid, int remap, const LevelMap &lm,       \
-                            hipStream_t st);                                                     \
-    hipError_t occupancy_step3d_m##m(int nw, bool adj, int *n);
+                            hipStream_t st);
 FWI_STEP3D_DECL(1)
 FWI_STEP3D_DECL(2)
 FWI_STEP3D_DECL(4)
@@ -985,21 +979,6 @@ FWI_STEP3D_DECL(8)
 #undef FWI_STEP3D_DECL
 void launch_step2d(int M, int nw, bool adj, const Job *jobs, const int *prefix, int njobs,
                    int step, int ttiles, int grid, int remap, const LevelMap &lm, hipStream_t st);
-
-// Resident blocks per CU of a 3-D step kernel (0 if the query fails).
-int step_blocks_per_cu(int M, int nw, bool adj)
-{
-    int n = 0;
-    hipError_t e = hipErrorInvalidValue;
-    switch (M) {
-    case 1: e = occupancy_step3d_m1(nw, adj, &n); break;
-    case 2: e = occupancy_step3d_m2(nw, adj, &n); break;
-    case 4: e = occupancy_step3d_m4(nw, adj, &n); break;
-    case 8: e = occupancy_step3d_m8(nw, adj, &n); break;
-    default: break;
-    }
-    return e == hipSuccess ? n : 0;
-}
 
 void launch_step(int ndim, int M, int nw, bool adj, const Job *jobs, const int *prefix,
                  int njobs, int step, int ttiles, int gblocks, int remap, const LevelMap &lm,
@@ -1090,14 +1069,6 @@ void launch_gather(const Job *jobs, const int *gprefix, int njobs, int gblocks, 
     if (gblocks > 0)
         hipLaunchKernelGGL(k_gather, dim3(gblocks), dim3(threads), 0, st, jobs, gprefix, njobs,
                            step, lm);
-}
-
-void launch_adj_inject(const Job *jobs, const int *gprefix, int njobs, int gblocks, int threads,
-                       int step, hipStream_t st)
-{
-    if (gblocks > 0)
-        hipLaunchKernelGGL(k_adj_inject, dim3(gblocks), dim3(threads), 0, st, jobs, gprefix,
-                           njobs, step);
 }
 
 int misfit_partials() { return 1024; }

@@ -41,8 +41,6 @@ void launch_snapshot(const Job *jobs, int njobs, int64_t fstride, int slot, int 
                      int mask, const LevelMap &lm, hipStream_t st);
 void launch_gather(const Job *jobs, const int *gprefix, int njobs, int gblocks, int threads,
                    int step, const LevelMap &lm, hipStream_t st);
-void launch_adj_inject(const Job *jobs, const int *gprefix, int njobs, int gblocks, int threads,
-                       int step, hipStream_t st);
 int misfit_partials();
 void launch_misfit(const float *d, const float *obs, float *res, int64_t n, double *partial,
                    double *out, hipStream_t st);
@@ -50,7 +48,6 @@ void launch_fold(int ndim, const Job *jobs, int njobs, int M, int gy, int nz, in
                  int nb, int nzm, int nym, int nxm, float *tmp1, float *tmp2, const float *v,
                  float *dv, hipStream_t st);
 int vstats_blocks();
-int step_blocks_per_cu(int M, int nw, bool adj);
 void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st);
 void launch_nonfinite_level(const Job *jobs, int njobs, int slot, float *partial, hipStream_t st);
 void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *levels,
@@ -269,12 +266,15 @@ int make_policy(const fwi_problem *p, const Geometry &g, int mode, const fwi_ckp
     }
 }
 
-// Upper bound on the tiles of one 2-D adjoint launch per shot (chunks are at
-// least one row): sizes the per-tile receiver lists before the tiling is
-// chosen.
-uint64_t max_adj_tiles_2d(const Geometry &g)
+// Receiver list bins of one shot: 64-column tiles (3-D: of kTile3dRows rows) x z.
+int list_tiles_y(const Geometry &g)
 {
-    return (uint64_t)((g.nx + g.M + kTileX - 1) / kTileX) * (uint64_t)g.nz;
+    return g.ndim == 3 ? (g.ny + kTile3dRows - 1) / kTile3dRows : 1;
+}
+uint64_t list_bins(const Geometry &g)
+{
+    return (uint64_t)((g.nx + g.M + kTileX - 1) / kTileX) * (uint64_t)list_tiles_y(g) *
+           (uint64_t)g.nz;
 }
 
 // Byte layout of the workspace (ws) and of the checkpoint buffer (ck).
@@ -283,6 +283,7 @@ struct Layout {
     uint64_t jobs = 0, prefix = 0, rec_off = 0, rec_next = 0, rec_head = 0, rt_start = 0, rt_rec = 0;
     uint64_t rt_key = 0, zrange = 0, stage = 0;
     uint64_t res = 0, partial = 0, misfit = 0, fold1 = 0, fold2 = 0, vstats = 0;
+    bool has_lists = false;
     bool ring_in_ws = false, has_adj = false, has_res = false, has_fold = false;
     uint64_t ws_total = 0, ck_total = 0;
 };
@@ -310,8 +311,9 @@ void make_layout(const fwi_problem *p, const Geometry &g, const Policy &po, int 
     L->rec_off = w.take(sizeof(int64_t) * S * R + 8);
     L->rec_next = w.take(sizeof(int32_t) * S * R + 4);
     L->rec_head = w.take(sizeof(int32_t) * S * R + 4);
-    if (g.ndim == 2) {
-        L->rt_start = w.take(sizeof(int32_t) * S * (max_adj_tiles_2d(g) + 1));
+    L->has_lists = g.ndim == 2 || mode == FWI_MODE_BACKWARD || mode == FWI_MODE_GRADIENT;
+    if (L->has_lists) {
+        L->rt_start = w.take(sizeof(int32_t) * S * (list_bins(g) + 1));
         L->rt_rec = w.take(sizeof(int32_t) * S * R + 4);
         L->rt_key = w.take(sizeof(int32_t) * S * R + 4);
     }
@@ -349,23 +351,6 @@ void make_layout(const fwi_problem *p, const Geometry &g, const Policy &po, int 
     L->ck_total = c.off;
 }
 
-// 3-D block shape code: 4 (4 wavefronts, 4 rows per thread), 8 (8, 4),
-// 42 (4 wavefronts, 2 rows per thread) or 82 (8, 2).  8th-order forward
-// launches default to 4 (188 registers, 2 waves per SIMD, 85 us per step on
-// a 304^3 grid; 82: 90 us, 42: 93 us).  The adjoint, which carries two
-// fields, and the 16th-order stencil, which needs twice the queue, default
-// to 42 (3 waves per SIMD; on the same grid the 8th-order fused adjoint
-// makes the 600-step gradient 0.207 s against 0.215 s with 82, the
-// 16th-order forward takes 101 against 129 us: 8-wave blocks of 3 waves per
-// SIMD leave one block per CU).
-int shape_code(bool adj, int M)
-{
-    if (const char *e = getenv(adj ? "FWI_WAVES_ADJ" : "FWI_WAVES")) {
-        const int v = atoi(e);
-        if (v == 4 || v == 8 || v == 42 || v == 82) return v;
-    }
-    return adj || M >= 8 ? 42 : 4;
-}
 // 2-D launches: grids too small to fill the GPU take the one-cell-per-lane
 // kernel with one-row tiles (shape code 1), whose launch is one round of load
 // latency; larger ones the marching kernel (code 4), which reads each field
@@ -446,32 +431,46 @@ int pipe_rows(const Geometry &g, int njobs, int ntx)
     return zc;
 }
 
-int block_waves(int code) { return code == 8 || code == 82 ? 8 : 4; }
-int block_rows(int code) { return code == 42 || code == 82 ? 2 : 4; }
+// 3-D launches of small grids take the kernel without marching (k_step3d_tile;
+// its fused adjoint up to 8th order).  Us per step, without marching against
+// with, 8th order: 80^3 padded 7.4 (8.6), 112^3 9.0 (9.8), 144^3 15.1 (19.6),
+// 176^3 20.6 (19.8), 240^3 43.5 (43.0), 304^3 94 (74.5).  At 16th order the halo
+// is twice as wide: 112^3 11.5 (13.3), 144^3 22.6 (22.5).  FWI_TILE3D sets the
+// largest number of cells.
+int64_t tile3d_cells(int M) { return M >= 8 ? 2000000 : 4000000; }
+int step_code(const Geometry &g, int njobs, bool adj)
+{
+    if (g.ndim == 2) return direct_2d(g, njobs) ? 1 : 4;
+    const char *split = getenv("FWI_SPLIT_ADJ");
+    if (adj && (g.M >= 8 || (split && atoi(split) != 0))) return kMarch3dCode;
+    const char *e = getenv("FWI_TILE3D");
+    const int64_t most = e ? atoll(e) : tile3d_cells(g.M);
+    return (int64_t)njobs * g.nz * g.ny * g.nx <= most ? kTile3dCode : kMarch3dCode;
+}
 
-void tiles_for(const Geometry &g, int njobs, bool adj, int *ntx, int *nty, int *nzc, int *zc)
+void tiles_for(const Geometry &g, int njobs, int code, int *ntx, int *nty, int *nzc, int *zc)
 {
     const int M = g.M;
-    const int code = shape_code(adj, g.M);
-    const int ty = block_rows(code) * block_waves(code);
     *ntx = (g.nx + M + kTileX - 1) / kTileX;
-    *nty = g.ndim == 3 ? (g.ny + ty - 1) / ty : 1;
+    *nty = g.ndim == 3 ? (g.ny + kTile3dRows - 1) / kTile3dRows : 1;
+    if (g.ndim == 3 && code == kTile3dCode) {
+        *zc = kTile3dPlanes;
+        *nzc = (g.nz + kTile3dPlanes - 1) / kTile3dPlanes;
+        return;
+    }
     const int64_t per = (int64_t)(*ntx) * (*nty) * njobs;
     int z;
     if (g.ndim == 3) {
-        // 3-D: the chunk count is chosen by how well the blocks fill whole
-        // waves of resident blocks (occupancy x CUs: a partial last wave idles
-        // part of the GPU) against the cost of short chunks (each warms its
-        // z-queue with 2M extra planes of the stencil field before its first
-        // plane).  Scored as (1 + M / zc) x (w + 7/8 (ceil(w) - w)) / w for w
-        // waves: the warm-up weighs twice its share of the bytes (it is also
-        // serial latency), and a partial last wave costs 7/8 of a full one
-        // (its blocks share the bandwidth among fewer).  The weights fit the
-        // measured chunk sweeps at 2 blocks per CU: 304^3 padded, 8th order:
-        // 5 chunks of 61 planes (475 blocks, 84.7 us; 38 planes 101 us, 76
-        // planes 95 us); 560 x 560 x 304: 3 chunks of 102 (forward 1.4 %
-        // faster than 8 of 38); a 128 x 1024 x 1024 slab: 4 chunks of 32
-        // (477 against 502 us with 6 of 22).  Chunks are at least 4 planes.
+        // 3-D marching: a CU's share is ceil(blocks / CUs) chunks, each of zc
+        // planes and the 2M planes that fill its z-queue; it runs three at a
+        // time, and a last one alone takes as long as 1.9 of three that share
+        // the CU (its loads are not hidden).  The chunk length with the least of
+        // that.  Measured, us per step: 304^3 padded, 8th order: 61 planes 74.8
+        // (2 chunks per CU, score 138), 38 76.8 (3; 138), 31 80.0 (4; 191), 44
+        // 83.1 (3; 156), 76 85.5 (2; 168), 51 90.1 (3; 177), 152 103 (1; 304);
+        // 560 x 560 x 304, forward and adjoint: 76 planes 885 (420), 51 904
+        // (472), 38 910 (501), 102 949 (539), 61 956 (545); 240^3: 30 43.0 (76), 60
+        // 46.1 (129).  Chunks are at least 4 planes.
         static int cus = 0;
         if (cus == 0) {
             int dev = 0;
@@ -480,23 +479,20 @@ void tiles_for(const Geometry &g, int njobs, bool adj, int *ntx, int *nty, int *
                 cus = prop.multiProcessorCount;
             if (cus <= 0) cus = 256;
         }
-        const int occ = std::max(1, step_blocks_per_cu(g.M, code, adj));
-        int64_t slots = (int64_t)occ * cus;
-        if (const char *e = getenv("FWI_TARGET_BLOCKS")) slots = std::max(1, atoi(e));
         double best = 0.0;
         z = g.nz;
         for (int n = 1; n <= std::max(1, g.nz / 4); ++n) {
             const int zc = (g.nz + n - 1) / n;
-            const int nc = (g.nz + zc - 1) / zc;
-            const double waves = (double)(per * nc) / (double)slots;
-            const double tail = (waves + 0.875 * (std::ceil(waves) - waves)) / waves;
-            const double score = (1.0 + (double)M / zc) * tail;
-            if (n == 1 || score < best - 1e-12) {
+            const int64_t blocks = per * ((g.nz + zc - 1) / zc);
+            const int64_t share = (blocks + cus - 1) / cus, rest = share % 3;
+            const double score = ((double)(share - rest) + (rest == 1 ? 1.9 : (double)rest)) *
+                                 (double)(zc + 2 * M);
+            if (n == 1 || score < best - 1e-9) {
                 best = score;
                 z = zc;
             }
         }
-    } else if (direct_2d(g, njobs)) {
+    } else if (code == 1) {
         *zc = 1;   // one-row tiles of the one-cell-per-lane kernel
         *nzc = g.nz;
         return;
@@ -531,7 +527,7 @@ int tile_flags(const Geometry &g)
 
 int gather_threads(const Geometry &g)
 {
-    return g.ndim == 3 ? 64 * block_waves(shape_code(false, g.M)) : 64;
+    return g.ndim == 3 ? kTile3dThreads : 64;
 }
 
 // ------------------------------------------------------------ call context
@@ -548,7 +544,7 @@ struct Ctx {
     int *d_prefix = nullptr;
     int ttiles = 0, atiles = 0, gblocks = 0, gthreads = 64;
     int remap = 1;
-    int nw = 4, nw_adj = 42;
+    int nw = 4, nw_adj = 4;   // step kernels (step_code)
     // several 2-D steps per launch: apron and tiles per shot of forward (0) and
     // adjoint (1) launches; the pair of fields that holds the newest forward
     // (FORWARD mode) and adjoint levels
@@ -594,9 +590,8 @@ int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws
     c.ck = static_cast<char *>(ckbuf);
     c.st = static_cast<hipStream_t>(stream);
     if (const char *e = getenv("FWI_XCD_REMAP")) c.remap = atoi(e) != 0;
-    c.nw = shape_code(false, c.g.M);
-    c.nw_adj = shape_code(true, c.g.M);
-    if (c.g.ndim == 2) c.nw = c.nw_adj = direct_2d(c.g, p->nshots) ? 1 : 4;
+    c.nw = step_code(c.g, p->nshots, false);
+    c.nw_adj = step_code(c.g, p->nshots, true);
     for (int a = 0; a < 2; ++a) {
         const int steps = a ? c.po.adj_steps : c.po.tb_steps;
         if (steps <= 0) continue;
@@ -666,8 +661,9 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     a.rec_off = reinterpret_cast<int64_t *>(c.ws + c.L.rec_off);
     a.rec_next = reinterpret_cast<int32_t *>(c.ws + c.L.rec_next);
     a.rec_head = reinterpret_cast<int32_t *>(c.ws + c.L.rec_head);
-    if (D == 2) {
-        a.bins = (int64_t)max_adj_tiles_2d(g) + 1;
+    a.nty = list_tiles_y(g);
+    if (c.L.has_lists) {
+        a.bins = (int64_t)list_bins(g) + 1;
         a.rt_start = reinterpret_cast<int32_t *>(c.ws + c.L.rt_start);
         a.rt_rec = reinterpret_cast<int32_t *>(c.ws + c.L.rt_rec);
         a.rt_key = reinterpret_cast<int32_t *>(c.ws + c.L.rt_key);
@@ -705,7 +701,7 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     c.jobs.assign(1, Job{});
     Job &J = c.jobs[0];
     for (int i = 0; i < 2; ++i) {
-        tiles_for(g, S, i == 1, &J.tile[i].ntx, &J.tile[i].nty, &J.tile[i].nzc, &J.tile[i].zc);
+        tiles_for(g, S, i ? c.nw_adj : c.nw, &J.tile[i].ntx, &J.tile[i].nty, &J.tile[i].nzc, &J.tile[i].zc);
         J.tile[i].ntiles = J.tile[i].ntx * J.tile[i].nty * J.tile[i].nzc;
         J.tile[i].flags = tile_flags(g);
     }
@@ -782,9 +778,6 @@ int adj_step(Ctx &c, int k, const LevelMap &lm = LevelMap{})
     if (c.plan) { plan_op(c, 2, k, 0, 0, lm); return FWI_OK; }
     launch_step(c.g.ndim, c.g.M, c.nw_adj, true, c.d_jobs, c.d_prefix + 2 * (c.p->nshots + 1),
                 c.p->nshots, -k, c.atiles, 0, c.remap, lm, c.st);
-    if (c.g.ndim == 3)   // 2-D adjoint steps add the adjoint source themselves
-        launch_adj_inject(c.d_jobs, c.d_prefix + c.p->nshots + 1, c.p->nshots, c.gblocks,
-                          c.gthreads, -k, c.st);
     return FWI_OK;
 }
 
@@ -1637,7 +1630,7 @@ int fwi_tile_probe(const float *cur, const float *prv, const float *kap, float *
         return fail(FWI_EINVAL, "plane too large for 32-bit offsets");
     if (zc == 0) {
         int ntx = 0, nty = 0, nzc = 0;
-        tiles_for(g, 1, false, &ntx, &nty, &nzc, &zc);
+        tiles_for(g, 1, kMarch3dCode, &ntx, &nty, &nzc, &zc);
     }
     zc = std::min(zc, nz);
     if (h_zc) *h_zc = zc;
@@ -1774,9 +1767,9 @@ int fwi_job_create(const fwi_problem *prob, int32_t kind, int32_t chunk, const f
 }
 
 // Launch groups of one advance: one per (dimension, order, direction, block
-// shape); 2-D jobs use two shapes, so at most 4 orders x 2 directions x
-// (2 + 1) = 24 groups.
-constexpr int kMaxGroups = 24;
+// shape); each dimension's jobs use two shapes, so at most 4 orders x 2
+// directions x 4 = 32 groups.
+constexpr int kMaxGroups = 32;
 
 int fwi_jobs_ws_bytes(int32_t njobs, int32_t ksteps, uint64_t *h_bytes)
 {
@@ -1998,8 +1991,6 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
                 const int ttiles = g.tp.back(), gblocks = g.gp.back();
                 launch_step(g.ndim, g.M, g.nw, g.adj != 0, g.d_jobs, g.d_prefix, n, j, ttiles,
                             g.adj ? 0 : gblocks, 1, LevelMap{}, st);
-                if (g.adj && g.ndim == 3)   // 2-D steps add the adjoint source themselves
-                    launch_adj_inject(g.d_jobs, g.d_prefix + n + 1, n, gblocks, g.gthreads, j, st);
             }
         }
         HIP_TRY(hipGetLastError());
