@@ -48,7 +48,8 @@ void launch_fold(int ndim, const Job *jobs, int njobs, int M, int gy, int nz, in
                  int nb, int nzm, int nym, int nxm, float *tmp1, float *tmp2, const float *v,
                  float *dv, hipStream_t st);
 int vstats_blocks();
-void launch_vstats(const float *v, int64_t n, float *partial, hipStream_t st);
+int range_blocks();
+void launch_vstats(const float *v, int64_t n, float *partial, int blocks, hipStream_t st);
 void launch_nonfinite_level(const Job *jobs, int njobs, int slot, float *partial, hipStream_t st);
 void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *levels,
                      hipStream_t st);
@@ -1179,7 +1180,7 @@ int check_level(Ctx &c, int L)
 int check_model(Ctx &c, const float *a)
 {
     float *d = c.f_at(c.L.vstats, true);
-    launch_vstats(a, c.g.model_cells, d, c.st);
+    launch_vstats(a, c.g.model_cells, d, vstats_blocks(), c.st);
     HIP_TRY(hipGetLastError());
     const int B = vstats_blocks();
     std::vector<float> h(3 * (size_t)B);
@@ -1571,12 +1572,12 @@ int fwi_velocity_range(const float *v, int64_t n, float *h_vmin, float *h_vmax, 
                        uint64_t ws_bytes, void *stream)
 {
     if (!v || n < 1 || !h_vmin || !h_vmax || !ws) return fail(FWI_EINVAL, "bad argument");
-    const int B = vstats_blocks();
+    const int B = range_blocks();
     if (ws_bytes < 4096 || ws_bytes < sizeof(float) * 3ull * B)
         return fail(FWI_ENOMEM, "workspace too small");
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *d = static_cast<float *>(ws);
-    launch_vstats(v, n, d, st);
+    launch_vstats(v, n, d, B, st);
     HIP_TRY(hipGetLastError());
     std::vector<float> h(3 * (size_t)B);
     HIP_TRY(hipMemcpyAsync(h.data(), d, h.size() * 4, hipMemcpyDeviceToHost, st));
