@@ -291,8 +291,10 @@ int fwi_revolve_plan(int32_t nsteps, int32_t slots, int32_t *h_ops, int64_t cap,
  * fwi_jobs_advance moves every job of a set forward by one chunk of
  * `ksteps` time steps of its current phase (forward, checkpoint recompute or
  * adjoint), putting the steps of all the jobs into shared launches: one
- * launch per time step per (dimension, order, direction), blocks indexed
- * over all the jobs' tiles.  Jobs join and leave between chunks.  Each job's
+ * launch per time step per (dimension, order, direction, kernel), blocks
+ * indexed over all the jobs' tiles.  Launches of different kinds run beside each
+ * other, on streams of the library that start behind `stream` and that it waits
+ * for.  Jobs join and leave between chunks.  Each job's
  * arithmetic is independent of which other jobs share its launches, so its
  * results are bitwise the same alone and in a mix.
  * ------------------------------------------------------------------------ */

@@ -16,6 +16,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -1834,6 +1835,138 @@ int run_ops(fwi_job *J, const std::vector<JobOp> &ops)
     return FWI_OK;
 }
 
+// Launch lanes of one fwi_jobs_advance: the caller's stream and up to kSide side
+// streams that run launch groups beside it.  Groups hold different jobs (those of
+// jobs stepping by rounds all go to lane 0), so their steps have no order among
+// each other.  One after the other, each launch ends with a chip that is partly
+// idle and small ones never fill it: 12 mixed jobs (2-D 64^2 - 256^2, 3-D 64^3 -
+// 96^3) took 39.8 ms on one stream, 27.5 ms on lanes; at four times the edge
+// 110 and 97 ms.
+//
+// The side streams start behind the caller's stream and it waits for them before
+// the call returns, whatever way the call ends, so for the caller everything is in
+// the order of its own stream.  (Behind it on the GPU: the host waits for nothing.)
+// Sets of side streams come from a pool of at most kSets per device, shared by all
+// threads; a set goes back when its call has enqueued its work, and serves any
+// caller next, in stream order.  Without a free set, or while the caller's stream
+// is captured into a graph, everything goes to the caller's stream, as with
+// FWI_LANES=1.
+class Lanes {
+public:
+    static constexpr int kSide = 3, kSets = 8;
+
+    Lanes(hipStream_t st, int want) : st_(st)
+    {
+        if (const char *e = getenv("FWI_LANES")) want = std::min(want, atoi(e));
+        want = std::min(want, kSide + 1);
+        if (want < 2) return;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+            !(set_ = take(st))) {
+            (void)hipGetLastError();
+            return;
+        }
+        bool ok = hipEventRecord(set_->fork, st) == hipSuccess;
+        for (int i = 0; ok && i < want - 1; ++i)
+            ok = hipStreamWaitEvent(set_->side[i], set_->fork, 0) == hipSuccess;
+        if (ok) n_ = want - 1;
+        else (void)hipGetLastError();
+    }
+    ~Lanes()
+    {
+        (void)join();
+        if (set_) {
+            std::lock_guard<std::mutex> l(pool().m);
+            set_->last = st_;
+            set_->busy = false;
+        }
+    }
+    Lanes(const Lanes &) = delete;
+    Lanes &operator=(const Lanes &) = delete;
+
+    int count() const { return n_ + 1; }
+    hipStream_t lane(int i) const { return i == 0 ? st_ : set_->side[i - 1]; }
+
+    // the caller's stream waits for the side streams
+    hipError_t join()
+    {
+        hipError_t err = hipSuccess;
+        for (int i = 0; i < n_; ++i) {
+            hipError_t e = hipEventRecord(set_->done[i], set_->side[i]);
+            if (e == hipSuccess) e = hipStreamWaitEvent(st_, set_->done[i], 0);
+            if (e != hipSuccess) {
+                err = e;
+                (void)hipStreamSynchronize(set_->side[i]);
+            }
+        }
+        n_ = 0;
+        return err;
+    }
+
+private:
+    struct Set {
+        hipStream_t side[kSide] = {};
+        hipEvent_t fork = nullptr, done[kSide] = {};
+        int device = 0;
+        hipStream_t last = nullptr;   // the caller it served last: preferred next time
+        bool busy = true;
+    };
+    struct Pool {
+        std::mutex m;
+        std::vector<Set *> sets;
+    };
+    // (never destroyed: the HIP runtime may be gone by then)
+    static Pool &pool()
+    {
+        static Pool *p = new Pool();
+        return *p;
+    }
+    static bool create(Set *s)
+    {
+        bool ok = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) == hipSuccess;
+        for (int i = 0; i < kSide; ++i)
+            ok = ok && hipStreamCreateWithFlags(&s->side[i], hipStreamNonBlocking) == hipSuccess &&
+                 hipEventCreateWithFlags(&s->done[i], hipEventDisableTiming) == hipSuccess;
+        if (ok) return true;
+        if (s->fork) (void)hipEventDestroy(s->fork);
+        for (int i = 0; i < kSide; ++i) {
+            if (s->side[i]) (void)hipStreamDestroy(s->side[i]);
+            if (s->done[i]) (void)hipEventDestroy(s->done[i]);
+        }
+        return false;
+    }
+    static Set *take(hipStream_t st)
+    {
+        int device = 0;
+        if (hipGetDevice(&device) != hipSuccess) return nullptr;
+        Pool &p = pool();
+        std::lock_guard<std::mutex> l(p.m);
+        Set *found = nullptr;
+        int made = 0;
+        for (Set *s : p.sets) {
+            if (s->device != device) continue;
+            ++made;
+            if (!s->busy && (!found || s->last == st)) found = s;
+        }
+        // a set that served another stream is taken only when there are kSets
+        if ((!found || found->last != st) && made < kSets) {
+            std::unique_ptr<Set> s(new Set());
+            s->device = device;
+            p.sets.reserve(p.sets.size() + 1);
+            if (create(s.get())) {
+                p.sets.push_back(s.get());
+                return s.release();
+            }
+        }
+        if (found) found->busy = true;
+        return found;
+    }
+
+    hipStream_t st_;
+    Set *set_ = nullptr;
+    int n_ = 0;
+};
+
 }  // namespace
 
 int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *ws,
@@ -1863,6 +1996,9 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
         };
         struct Group {
             int ndim = 0, M = 0, adj = 0, nw = 4, steps = 0;
+            bool rounds = false;        // holds a job stepping by rounds
+            double cells = 0;
+            int lane = 0;
             std::vector<Entry> table;
             std::vector<int> tp{0}, gp{0};
             std::vector<int32_t> lev;   // level lists, ksteps per entry that has one
@@ -1886,8 +2022,10 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
             Group &g = group_of(J->c.g.ndim, J->c.g.M, isadj, isadj ? J->c.nw_adj : J->c.nw);
             g.steps = std::max(g.steps, steps);
             g.gthreads = J->c.gthreads;
+            g.cells += (double)t.nz * t.ny * t.nx;
             Entry x = e;
             if (lev) {
+                g.rounds = true;
                 x.levoff = (int)g.lev.size();
                 g.lev.insert(g.lev.end(), lev, lev + ksteps);
             }
@@ -1981,6 +2119,27 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
             }
         }
         HIP_TRY(hipGetLastError());
+        // groups to lanes, the longest first, each to the lane with the least work
+        // (cell steps, an adjoint one counted twice for its second stencil)
+        int chains = 0;
+        bool any_rounds = false;
+        std::vector<Group *> order;
+        for (Group &g : groups) {
+            if (g.rounds) any_rounds = true;
+            else order.push_back(&g);
+        }
+        chains = (int)order.size() + (any_rounds ? 1 : 0);
+        auto work = [](const Group &g) { return g.cells * g.steps * (g.adj ? 2 : 1); };
+        std::sort(order.begin(), order.end(),
+                  [&](const Group *a, const Group *b) { return work(*a) > work(*b); });
+        Lanes lanes(st, chains);
+        std::vector<double> load(lanes.count(), 0.);
+        for (const Group &g : groups)
+            if (g.rounds) load[0] += work(g);
+        for (Group *g : order) {
+            g->lane = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            load[g->lane] += work(*g);
+        }
         for (int j = 0; j < ksteps; ++j) {
             // per-job operations between this job's rounds (snapshot and
             // restore copies of binomial checkpointing), in stream order
@@ -1991,10 +2150,11 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
                 const int n = (int)g.table.size();
                 const int ttiles = g.tp.back(), gblocks = g.gp.back();
                 launch_step(g.ndim, g.M, g.nw, g.adj != 0, g.d_jobs, g.d_prefix, n, j, ttiles,
-                            g.adj ? 0 : gblocks, 1, LevelMap{}, st);
+                            g.adj ? 0 : gblocks, 1, LevelMap{}, lanes.lane(g.lane));
             }
         }
         HIP_TRY(hipGetLastError());
+        HIP_TRY(lanes.join());
         // 4. operations due right after this chunk (final gather, residual, fold)
         for (int i = 0; i < njobs; ++i) {
             if (jobs[i]->rounds) TRY(run_ops(jobs[i], plans[i].before[ksteps]));
