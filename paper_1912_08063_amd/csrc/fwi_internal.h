@@ -31,7 +31,7 @@ constexpr int32_t kTileZAlt = 2;
 // tile rows, and the planes of a tile without marching.
 // Receiver lists of 3-D jobs are by 64 columns x kTile3dRows rows x 1 plane, their
 // keys plane << kKeyBits3d | row << 6 | column.
-constexpr int kTile3dCode = 3, kMarch3dCode = 4, kTile3dRows = 16, kTile3dPlanes = 4, kTile3dThreads = 256;
+constexpr int kTile3dCode = 3, kMarch3dCode = 4, kTile3dRows = 16, kTile3dPlanes = 2, kTile3dThreads = 256;
 constexpr int kKeyBits3d = 10;
 
 // Size of the fixed per-GPU workspace of fwi_forward_noalloc.

@@ -434,12 +434,14 @@ int pipe_rows(const Geometry &g, int njobs, int ntx)
 }
 
 // 3-D launches of small grids take the kernel without marching (k_step3d_tile;
-// its fused adjoint up to 8th order).  Us per step, without marching against
-// with, 8th order: 80^3 padded 7.4 (8.6), 112^3 9.0 (9.8), 144^3 15.1 (19.6),
-// 176^3 20.6 (19.8), 240^3 43.5 (43.0), 304^3 94 (74.5).  At 16th order the halo
-// is twice as wide: 112^3 11.5 (13.3), 144^3 22.6 (22.5).  FWI_TILE3D sets the
-// largest number of cells.
-int64_t tile3d_cells(int M) { return M >= 8 ? 2000000 : 4000000; }
+// its fused adjoint up to 8th order).  Us per step, without marching (with).  8th
+// order forward: 80^3 padded cells 6.3 (7.1), 112^3 8.2 (8.1), 144^3 14.7 (15.4),
+// 176^3 19.8 (20.0), 208^3 31.8 (35.8), 256^3 57 (55); gradient, every step
+// recomputed once: 80^3 20.5 (25.1), 144^3 58.8 (62.2), 208^3 136 (142), 232^3 177
+// (170), 256^3 288 (232).  At 16th order the halo is twice as wide: 64^3 6.5 (9.4),
+// 80^3 8.1 (9.7), 88^3 11.4 (10.9), 112^3 12.7 (11.4).  FWI_TILE3D sets the largest
+// number of cells.
+int64_t tile3d_cells(int M) { return M >= 8 ? 600000 : 10000000; }
 int step_code(const Geometry &g, int njobs, bool adj)
 {
     if (g.ndim == 2) return direct_2d(g, njobs) ? 1 : 4;
