@@ -142,13 +142,12 @@ inline int tb_tiles(int cells, int w, int a)
     return cells <= w ? 1 : (cells - w + (w - 2 * a) - 1) / (w - 2 * a) + 1;
 }
 
-// One multi-step 2-D launch.
-
+// One multi-step 2-D launch: jobs of one grid at one level.
 struct TbLaunch {
-    int32_t tiles_per_job;   // jobs of one grid and level (0: the prefix array's)
+    int32_t tiles_per_job;
     uint32_t magic_job, magic_tx;   // tb_magic of tiles_per_job and ntx
-    int32_t ntx, ntz;        // tiles in x and z (tiles_per_job > 0)
-    int32_t step;            // the level itself (tiles_per_job > 0), or the chunk's step
+    int32_t ntx, ntz;        // tiles in x and z
+    int32_t step;            // the level
     int32_t kk;              // steps
     int32_t A;               // apron
     int32_t pair;            // fields to read: adjoint pair, forward pair (-1: ring)

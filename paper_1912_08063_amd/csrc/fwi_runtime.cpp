@@ -56,8 +56,8 @@ void launch_assemble(const AssembleArgs &a, Job *table, int *prefix, int32_t *le
                      hipStream_t st);
 int tb2d_width(int shape);
 int tb2d_height(int shape);
-void launch_step2d_tb(int M, int shape, bool adj, const Job *jobs, const int *prefix, int njobs,
-                      int ttiles, const TbLaunch &a, hipStream_t st);
+void launch_step2d_tb(int M, int shape, bool adj, const Job *jobs, int njobs, const TbLaunch &a,
+                      hipStream_t st);
 int pipe2d_width();
 int pipe2d_group(int M);
 void launch_step2d_pipe(int M, const Job *jobs, int njobs, const PipeLaunch &a, hipStream_t st);
@@ -803,7 +803,7 @@ void tb_launch(Ctx &c, bool adj, int n, int kk, int pair, bool record, bool stor
     a.remap = c.remap;
     a.record = record;
     a.store_all = store_all;
-    launch_step2d_tb(c.g.M, c.po.tb_shape, adj, c.d_jobs, nullptr, S, T * S, a, c.st);
+    launch_step2d_tb(c.g.M, c.po.tb_shape, adj, c.d_jobs, S, a, c.st);
 }
 
 // Steps n = a .. b-1, several per 2-D launch where the call allows it

@@ -420,9 +420,8 @@ __device__ __forceinline__ int tb_div(int b, int d, uint32_t m)
 
 template <int M, int W, int H, int PZ, bool ADJ>
 __global__ __launch_bounds__((W / 4) * (H / PZ)) void k_step2d_tb(
-    const Job *__restrict__ jobs, const int *__restrict__ prefix, int njobs, int tiles_per_job,
-    uint32_t magic_job, uint32_t magic_tx, int nt_x, int nt_z, int step, int steps_apron,
-    int flags)
+    const Job *__restrict__ jobs, int njobs, int tiles_per_job, uint32_t magic_job,
+    uint32_t magic_tx, int ntx, int ntz, int step, int steps_apron, int flags)
 {
     constexpr int NT = (W / 4) * (H / PZ), NR = W * H;
     constexpr int XP = (M + 3) / 4 * 4;                // columns read beside a patch
@@ -437,30 +436,12 @@ __global__ __launch_bounds__((W / 4) * (H / PZ)) void k_step2d_tb(
     const int tid = threadIdx.x;
     int b = blockIdx.x;
     if (flags & kTbRemap) b = xcd_remap(b, gridDim.x);
-    int j, local, ntx, ntz, tx, tz, n, kk = steps_apron & 0xffff;
-    const Job *__restrict__ J;
-    const int A = steps_apron >> 16, pair = (flags & 3) - 1;
-    if (tiles_per_job > 0) {   // every job has the same grid and level
-        j = njobs > 1 ? tb_div(b, tiles_per_job, magic_job) : 0;
-        local = b - j * tiles_per_job;
-        J = jobs + j;
-        n = step;
-        ntx = nt_x;
-        ntz = nt_z;
-        tz = ntx > 1 ? tb_div(local, ntx, magic_tx) : local;
-    } else {
-        j = find_job(prefix, njobs, b);
-        local = b - prefix[j];
-        J = jobs + j;
-        n = step_level(J, step, ADJ);
-        // this job's steps of the launch
-        kk = ADJ ? min(kk, n - J->adj_lo + 1) : min(kk, J->fwd_hi - n);
-        if (kk <= 0) return;
-        ntx = tb_tiles(J->nx + 2 * M, W, A);
-        ntz = tb_tiles(J->nz + 2 * M, H, A);
-        tz = local / ntx;
-    }
-    tx = local - tz * ntx;
+    // (every job has the same grid and level)
+    const int kk = steps_apron & 0xffff, A = steps_apron >> 16, pair = (flags & 3) - 1;
+    const int j = njobs > 1 ? tb_div(b, tiles_per_job, magic_job) : 0;
+    const int local = b - j * tiles_per_job, n = step;
+    const Job *__restrict__ J = jobs + j;
+    const int tz = ntx > 1 ? tb_div(local, ntx, magic_tx) : local, tx = local - tz * ntx;
     const int nz = J->nz, nx = J->nx, pitch = J->pitch, nb = J->nb, nrec = J->nrec;
     const int64_t fstride = J->fstride;
     float *const ring = J->ring, *const adj = J->adj, *const grad = J->grad;
@@ -1144,8 +1125,8 @@ int tb2d_height(int shape)
 }
 
 template <int M, bool ADJ>
-static void launch_tb(int shape, dim3 g, const Job *jobs, const int *prefix, int njobs,
-                      const TbLaunch &a, hipStream_t st)
+static void launch_tb(int shape, dim3 g, const Job *jobs, int njobs, const TbLaunch &a,
+                      hipStream_t st)
 {
     const int flags = (a.pair + 1) | (a.remap ? kTbRemap : 0) | (a.record ? kTbRecord : 0) |
                       (a.store_all ? kTbStoreAll : 0);
@@ -1154,24 +1135,24 @@ static void launch_tb(int shape, dim3 g, const Job *jobs, const int *prefix, int
     case id:                                                                                    \
         if constexpr (tb_has_shape(M, id))                                                      \
             hipLaunchKernelGGL((k_step2d_tb<M, W, H, PZ, ADJ>), g, dim3((W / 4) * (H / PZ)), 0, \
-                               st, jobs, prefix, njobs, a.tiles_per_job, a.magic_job,           \
-                               a.magic_tx, a.ntx, a.ntz, a.step, a.kk | a.A << 16, flags);      \
+                               st, jobs, njobs, a.tiles_per_job, a.magic_job, a.magic_tx,       \
+                               a.ntx, a.ntz, a.step, a.kk | a.A << 16, flags);                  \
         break;
         FWI_TB_SHAPES(FWI_TB)
 #undef FWI_TB
     }
 }
 
-void launch_step2d_tb(int M, int shape, bool adj, const Job *jobs, const int *prefix, int njobs,
-                      int ttiles, const TbLaunch &a, hipStream_t st)
+void launch_step2d_tb(int M, int shape, bool adj, const Job *jobs, int njobs, const TbLaunch &a,
+                      hipStream_t st)
 {
-    if (ttiles <= 0) return;
-    const dim3 g(ttiles);
+    const dim3 g(a.tiles_per_job * njobs);
+    if (g.x == 0) return;
     switch (M) {
 #define FWI_TBM(m)                                                             \
     case m:                                                                    \
-        if (adj) launch_tb<m, true>(shape, g, jobs, prefix, njobs, a, st);     \
-        else launch_tb<m, false>(shape, g, jobs, prefix, njobs, a, st);        \
+        if (adj) launch_tb<m, true>(shape, g, jobs, njobs, a, st);             \
+        else launch_tb<m, false>(shape, g, jobs, njobs, a, st);                \
         break;
         FWI_TBM(1)
         FWI_TBM(2)
