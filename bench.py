@@ -714,7 +714,7 @@ def main():
                                               / (ms * 1e-3) / 1e9, 3),
         },
         "roofline": {
-            "bound": "hbm", "kernel": "k_step3d<4,0,4,4> (forward stencil step, one launch per time step)",
+            "bound": "hbm", "kernel": "k_step3d<4,0> (forward stencil step, one launch per time step)",
             "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": recorded_traffic(),
             "bytes_per_launch": bytes_per_launch,

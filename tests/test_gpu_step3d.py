@@ -74,3 +74,23 @@ def test_a_receiver_in_every_cell_of_a_plane(kernel, monkeypatch):
     omis, odv = oracle_gradient(P, P.v, obs)
     assert rel_l2(tr, oracle_forward(P)) <= 1e-4
     assert abs(mis - omis) <= 1e-3 * omis and rel_l2(dv, odv) <= 1e-3
+
+
+@pytest.mark.parametrize("order", [2, 8, 16])
+def test_chunk_directions_and_order_bitwise_equal(order, monkeypatch):
+    """Odd chunks marching down (the default) or up, the chunks of a column
+    consecutive or not, for chunks of one plane to a short last one."""
+    P = _problem((21, 19, 70), order)
+    obs = _obs(P)
+    monkeypatch.setenv("FWI_TILE3D", "0")
+    for chunk in ("1", "7", "16", "30"):
+        monkeypatch.setenv("FWI_ZCHUNK", chunk)
+        runs = []
+        for alt, fast in (("1", "0"), ("0", "0"), ("1", "1"), ("0", "1")):
+            monkeypatch.setenv("FWI_ZALT", alt)
+            monkeypatch.setenv("FWI_ZFAST", fast)
+            runs.append((gpu_forward(P), gpu_gradient(P, P.v, obs, "every:8")))
+        assert np.any(runs[0][0]) and np.any(runs[0][1][1])
+        for tr, (mis, dv, _) in runs[1:]:
+            assert np.array_equal(tr, runs[0][0]), chunk
+            assert mis == runs[0][1][0] and np.array_equal(dv, runs[0][1][1]), chunk
