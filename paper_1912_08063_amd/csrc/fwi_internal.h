@@ -36,6 +36,8 @@ constexpr int kKeyBits3d = 10;
 
 // Size of the fixed per-GPU workspace of fwi_forward_noalloc.
 constexpr uint64_t kScratchBytes = 128ull << 20;
+// Room beside it for the staging records of a call, which do not count against it.
+constexpr uint64_t kScratchSlack = 1ull << 20;
 
 struct Job {
     // geometry of the padded grid and its field layout

@@ -1003,7 +1003,7 @@ __global__ __launch_bounds__(256) void k_nonfinite_level(const Job *__restrict__
 // process ends.  Host code never passes the array's name to a kernel (on the
 // host it is only a stand-in for the symbol): it looks up each device's own
 // address once, with that device current, and passes that address.
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSlack];
 
 int scratch_address(void **ptr)
 {

@@ -285,6 +285,7 @@ struct Layout {
     uint64_t jobs = 0, prefix = 0, rec_off = 0, rec_next = 0, rec_head = 0, rt_start = 0, rt_rec = 0;
     uint64_t rt_key = 0, zrange = 0, stage = 0;
     uint64_t res = 0, partial = 0, misfit = 0, fold1 = 0, fold2 = 0, vstats = 0;
+    uint64_t staging = 0;   // bytes of zrange, stage and vstats
     bool has_lists = false;
     bool ring_in_ws = false, has_adj = false, has_res = false, has_fold = false;
     uint64_t ws_total = 0, ck_total = 0;
@@ -319,9 +320,11 @@ void make_layout(const fwi_problem *p, const Geometry &g, const Policy &po, int 
         L->rt_rec = w.take(sizeof(int32_t) * S * R + 4);
         L->rt_key = w.take(sizeof(int32_t) * S * R + 4);
     }
+    const uint64_t before = w.off;
     L->zrange = w.take(sizeof(int32_t) * 2 * S);
     L->stage = w.take(sizeof(StageResult));
     L->vstats = w.take(sizeof(float) * 3ull * vstats_blocks());
+    L->staging = w.off - before;
     if (mode == FWI_MODE_BACKWARD || mode == FWI_MODE_GRADIENT) {
         L->has_adj = true;
         L->adj = w.take((po.adj_steps > 0 ? 4 : 2) * fb * S);
@@ -1472,7 +1475,7 @@ int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *sr
         TRY(make_geometry(prob, &g));
         TRY(make_policy(prob, g, FWI_MODE_FORWARD, nullptr, &po, false));
         make_layout(prob, g, po, FWI_MODE_FORWARD, &L);
-        need = L.ws_total;
+        need = L.ws_total - std::min(L.staging, kScratchSlack);
         tb = false;
     }
     if (need > kScratchBytes)
@@ -1483,7 +1486,8 @@ int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *sr
     void *ws = nullptr;
     if (scratch_address(&ws) != 0)
         return fail(FWI_EHIP, "fwi_forward_noalloc: no address for the fixed workspace");
-    return forward_call(prob, v, src, src_pos, rec_pos, traces, ws, kScratchBytes, stream, tb);
+    return forward_call(prob, v, src, src_pos, rec_pos, traces, ws, kScratchBytes + kScratchSlack, stream,
+                        tb);
 }
 
 int fwi_forward_ckpt(const fwi_problem *prob, const float *v, const float *src,
