@@ -100,6 +100,7 @@ struct StageResult {
     float vmin, vmax, bad_v;         // velocity range, non-finite cells
     int32_t duplicates;              // receivers share a cell
     int64_t bad_src, bad_rec;        // first position outside the model
+    int32_t map_set, reserved;       // the map was written (map_is_output only)
 };
 struct StageArgs {
     const float *v;
@@ -110,6 +111,11 @@ struct StageArgs {
     const int32_t *src_pos, *rec_pos;
     int32_t *map;                    // scratch: a field per shot, mstride apart
     int64_t mstride;
+    // the map lies in an output of the call (forward_ckpt's checkpoint buffer), so
+    // it is written only if the host will accept the call: v_max dt / dx up to
+    // cfl_max and the other checks of StageResult
+    int32_t map_is_output;
+    double dt, dx, cfl_max;
     int64_t *rec_off;
     int32_t *rec_next, *rec_head;
     int64_t bins;                    // list bounds per shot (tiles x nz + 1; 0: no lists)

@@ -358,6 +358,7 @@ __global__ __launch_bounds__(256) void k_stage_begin(StageArgs a)
         if (i0 == 0) {
             a.result->bad_src = a.result->bad_rec = 0x7fffffffffffffffll;
             a.result->duplicates = 0;
+            a.result->map_set = 0;
         }
         for (int64_t i = i0; i < (int64_t)a.S * a.bins; i += n) a.rt_start[i] = 0;
         for (int64_t i = i0; i < a.S; i += n) {
@@ -369,8 +370,9 @@ __global__ __launch_bounds__(256) void k_stage_begin(StageArgs a)
     block_stats(a.v, a.ncells, blockIdx.x, B, a.partial);
 }
 
-// Bounds of every source and receiver (the first one outside the model),
-// receiver offsets (-1: outside), and their map cells set to "no receiver".
+// Bounds of every source and receiver (the first one outside the model) and
+// receiver offsets (-1: outside); their map cells are set to "no receiver" here
+// unless the map is an output.  Block 0 also reduces the model statistics.
 __global__ __launch_bounds__(256) void k_stage_positions(StageArgs a)
 {
     const int64_t n = (int64_t)a.S * a.R;
@@ -394,13 +396,53 @@ __global__ __launch_bounds__(256) void k_stage_positions(StageArgs a)
         const int z = q[0] + a.nb, y = a.D == 3 ? q[1] + a.nb : 0, x = q[a.D - 1] + a.nb;
         const int64_t off = ((int64_t)(z + a.M) * a.nya + (y + a.gy)) * a.pitch + (x + a.M);
         a.rec_off[i] = off;
-        a.map[i / a.R * a.mstride + off] = 0x7fffffff;
+        if (!a.map_is_output) a.map[i / a.R * a.mstride + off] = 0x7fffffff;
     }
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        float lo = INFINITY, hi = -INFINITY, bad = 0.f;
+        for (int i = threadIdx.x; i < a.vblocks; i += 64) {
+            lo = fminf(lo, a.partial[i]);
+            hi = fmaxf(hi, a.partial[a.vblocks + i]);
+            bad += a.partial[2 * a.vblocks + i];
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o));
+            hi = fmaxf(hi, __shfl_xor(hi, o));
+            bad += __shfl_xor(bad, o);
+        }
+        if (threadIdx.x == 0) {
+            a.result->vmin = lo;
+            a.result->vmax = hi;
+            a.result->bad_v = bad;
+        }
+    }
+}
+
+// Whether the map may be written (the host's checks in stage(), in its order).
+__device__ __forceinline__ bool map_writable(const StageArgs &a)
+{
+    if (!a.map_is_output) return true;
+    const StageResult &r = *a.result;
+    return r.bad_src == 0x7fffffffffffffffll && r.bad_rec == 0x7fffffffffffffffll &&
+           !(r.bad_v > 0.f) && r.vmin > 0.f && !((double)r.vmax * a.dt / a.dx > a.cfl_max);
+}
+
+// The receivers' map cells set to "no receiver", for a map that is an output: a
+// refused call leaves it as it was.
+__global__ __launch_bounds__(256) void k_stage_clear(StageArgs a)
+{
+    if (!map_writable(a)) return;
+    const int64_t n = (int64_t)a.S * a.R;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.result->map_set = 1;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        a.map[i / a.R * a.mstride + a.rec_off[i]] = 0x7fffffff;
 }
 
 // The first receiver of every receiver cell.
 __global__ __launch_bounds__(256) void k_stage_first(StageArgs a)
 {
+    if (!map_writable(a)) return;
     const int64_t n = (int64_t)a.S * a.R;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -437,10 +479,10 @@ __device__ __forceinline__ void bin_run(int64_t bin, int &first, int &len)
     len = (after ? lane + __ffsll((long long)after) : 64) - first;
 }
 
-// Heads, and the receiver cells of each list bin; block 0
-// also reduces the model statistics.
+// Heads, and the receiver cells of each list bin.
 __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
 {
+    if (!map_writable(a)) return;
     const int64_t n = (int64_t)a.S * a.R;
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < n;
          i0 += (int64_t)gridDim.x * blockDim.x) {
@@ -466,24 +508,6 @@ __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
                 if (z + 1 > zr[1]) atomicMax(zr + 1, z + 1);
                 atomicAdd(a.rt_start + bin, len);
             }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 64) {
-        float lo = INFINITY, hi = -INFINITY, bad = 0.f;
-        for (int i = threadIdx.x; i < a.vblocks; i += 64) {
-            lo = fminf(lo, a.partial[i]);
-            hi = fmaxf(hi, a.partial[a.vblocks + i]);
-            bad += a.partial[2 * a.vblocks + i];
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = fminf(lo, __shfl_xor(lo, o));
-            hi = fmaxf(hi, __shfl_xor(hi, o));
-            bad += __shfl_xor(bad, o);
-        }
-        if (threadIdx.x == 0) {
-            a.result->vmin = lo;
-            a.result->vmax = hi;
-            a.result->bad_v = bad;
         }
     }
 }
@@ -1044,7 +1068,9 @@ void launch_stage_check(const StageArgs &a, hipStream_t st)
     hipLaunchKernelGGL(k_stage_begin, dim3(a.vblocks + blocks((int64_t)a.S * std::max<int64_t>(a.bins, 1))),
                        dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_stage_positions, dim3(blocks(n + a.S)), dim3(256), 0, st, a);
-    if (n > 0) hipLaunchKernelGGL(k_stage_first, dim3(blocks(n)), dim3(256), 0, st, a);
+    if (n == 0) return;
+    if (a.map_is_output) hipLaunchKernelGGL(k_stage_clear, dim3(blocks(n)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_stage_first, dim3(blocks(n)), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_stage_heads, dim3(blocks(n)), dim3(256), 0, st, a);
 }
 

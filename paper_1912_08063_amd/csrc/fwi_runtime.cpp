@@ -670,6 +670,11 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     // an adjoint field, or (forward calls) the ring's level 0
     a.map = reinterpret_cast<int32_t *>(adj ? adj : ring);
     a.mstride = (int64_t)(fs * (adj ? adj_fields : c.po.R));
+    const double lim = std::sqrt(4.0 / (p->ndim * max_symbol(p->order)));
+    a.map_is_output = !adj && !c.L.ring_in_ws;
+    a.dt = p->dt;
+    a.dx = p->dx;
+    a.cfl_max = lim;
     a.rec_off = reinterpret_cast<int64_t *>(c.ws + c.L.rec_off);
     a.rec_next = reinterpret_cast<int32_t *>(c.ws + c.L.rec_next);
     a.rec_head = reinterpret_cast<int32_t *>(c.ws + c.L.rec_head);
@@ -696,8 +701,9 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     if (h.bad_v > 0.f) return fail(FWI_EINVAL, "velocity has non-finite values");
     if (!(vmin > 0.f)) return fail(FWI_EINVAL, "velocity must be > 0 (min %g)", (double)vmin);
     const double cfl = (double)vmax * p->dt / p->dx;
-    const double lim = std::sqrt(4.0 / (p->ndim * max_symbol(p->order)));
-    if (cfl > lim) return fail(FWI_ECFL, "v_max dt / dx = %.4f exceeds %.4f", cfl, lim);
+    // (the device's own check decides whether a map in an output was written)
+    if (cfl > lim || (a.map_is_output && R > 0 && !h.map_set))
+        return fail(FWI_ECFL, "v_max dt / dx = %.4f exceeds %.4f", cfl, lim);
     // sponge strength: as given, or (eta_max < 0) the default for this model
     const double eta_max = p->eta_max >= 0.f ? (double)p->eta_max
                                              : default_eta_max(vmax, g.nb, p->dx);
