@@ -79,7 +79,7 @@ struct Job {
     const float *wavelet;  // [nt]
     const int64_t *rec_off;    // [nrec] field offsets of the receiver cells
     const int32_t *rec_next;   // [nrec] next receiver on the same cell, -1 at the end
-    const int32_t *rec_head;   // [nrec] 1 for the first receiver of its cell
+    const int32_t *rec_head;   // [nrec] the first receiver of its cell
     // receiver lists: the first receiver of each receiver cell, sorted by tile
     // (64 columns; 3-D: x kTile3dRows rows) and z; rows (planes) z0 .. z1-1 of tile
     // t own entries rt_start[t nz + z0] .. rt_start[t nz + z1] - 1 of rt_rec

@@ -491,8 +491,10 @@ __global__ __launch_bounds__(256) void k_stage_heads(StageArgs a)
         int z = 0, key = 0;
         if (i < n) {
             const int64_t off = a.rec_off[i], s = i / a.R;
-            const int head = off >= 0 && a.map[s * a.mstride + off] == (int)(i - s * a.R);
-            a.rec_head[i] = head;
+            const int r = (int)(i - s * a.R);
+            const int first_r = off >= 0 ? a.map[s * a.mstride + off] : r;
+            const bool head = off >= 0 && first_r == r;
+            a.rec_head[i] = first_r;
             a.rec_next[i] = -1;
             if (off >= 0 && !head) a.result->duplicates = 1;
             if (a.bins > 0 && head) bin = s * a.bins + list_bin(a, off, z, key) + 1;
@@ -549,7 +551,8 @@ __global__ __launch_bounds__(256) void k_stage_lists(StageArgs a)
         const int64_t i = i0 + threadIdx.x, s = i < n ? i / a.R : 0;
         int64_t bin = -1;
         int z = 0, key = 0, first, len, p = 0;
-        if (i < n && a.rec_head[i]) bin = s * a.bins + list_bin(a, a.rec_off[i], z, key) + 1;
+        if (i < n && a.rec_head[i] == (int)(i - s * a.R))
+            bin = s * a.bins + list_bin(a, a.rec_off[i], z, key) + 1;
         bin_run(bin, first, len);
         const int lane = threadIdx.x & 63;
         // (the order within a bin does not matter: its cells are distinct)

@@ -62,6 +62,7 @@ int pipe2d_width();
 int pipe2d_group(int M);
 void launch_step2d_pipe(int M, const Job *jobs, int njobs, const PipeLaunch &a, hipStream_t st);
 void launch_gather2(const Job *jobs, int njobs, int nrec, int n, int s0, int s1, hipStream_t st);
+void launch_trace_duplicates(const Job *jobs, int njobs, int nrec, int nt, hipStream_t st);
 int scratch_address(void **ptr);
 void launch_stream_probe(const float *a, const float *b, const float *c, float *o, int64_t n,
                          int variant, hipStream_t st);
@@ -564,6 +565,7 @@ struct Ctx {
     int fwd_pair = 0, adj_pair = 0;
     // two-step marching forward launches: column tiles, rows per chunk (0: none)
     int pipe_ntx = 0, pipe_zc = 0;
+    bool duplicates = false;   // receivers share a cell
     std::vector<int> slot_time;
     // plan mode (host only): launches are recorded here instead of issued,
     // ten int32 per launch (see fwi_revolve_plan)
@@ -619,8 +621,8 @@ int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws
 }
 
 // Receivers that share a cell: each one's next receiver on the cell, in index
-// order (rec_next; the first of a cell is its head).  Sorted on the host, since
-// only calls with such receivers need it.
+// order (rec_next).  Sorted on the host, since only calls with such receivers need
+// it.
 int stage_duplicates(Ctx &c, const StageArgs &a)
 {
     const size_t S = (size_t)a.S, R = (size_t)a.R;
@@ -707,7 +709,8 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     // sponge strength: as given, or (eta_max < 0) the default for this model
     const double eta_max = p->eta_max >= 0.f ? (double)p->eta_max
                                              : default_eta_max(vmax, g.nb, p->dx);
-    if (h.duplicates) {
+    c.duplicates = h.duplicates != 0;
+    if (c.duplicates) {
         const int st = stage_duplicates(c, a);
         if (st) return st;
     }
@@ -1107,6 +1110,8 @@ int forward_phase(Ctx &c, bool record)
     if (record && c.po.tb_steps <= 0)   // multi-step launches sample what they compute
         launch_gather(c.d_jobs, c.d_prefix + c.p->nshots + 1, c.p->nshots, c.gblocks,
                       c.gthreads, nt, LevelMap{}, c.st);
+    else if (record && c.duplicates)
+        launch_trace_duplicates(c.d_jobs, c.p->nshots, c.p->nrec, nt, c.st);
     HIP_TRY(hipGetLastError());
     return FWI_OK;
 }
