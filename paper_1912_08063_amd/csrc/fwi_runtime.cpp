@@ -218,14 +218,14 @@ struct Policy {
 struct TbConfig {
     int shape, steps;
 };
-TbConfig tb_config(const Geometry &g, int njobs);
+TbConfig tb_config(const Geometry &g, int njobs, bool adjoint);
 
 // tb: whether several 2-D steps may share a launch (they need two more fields)
 int make_policy(const fwi_problem *p, const Geometry &g, int mode, const fwi_ckpt *ck, Policy *po,
                 bool tb = true)
 {
     *po = Policy{};
-    const TbConfig tc = tb ? tb_config(g, p->nshots) : TbConfig{0, 0};
+    const TbConfig tc = tb ? tb_config(g, p->nshots, mode != FWI_MODE_FORWARD) : TbConfig{0, 0};
     const int tbk = tc.steps;
     po->tb_shape = tc.shape;
     if (mode == FWI_MODE_FORWARD) {
@@ -384,9 +384,17 @@ bool direct_2d(const Geometry &g, int njobs)
 // 128 x 128: 2040 against 2675, and 1024 x 320 is fastest with one (4119 against
 // 4267); four shots of 303 x 555: 128 x 64 with four rows per thread 7185 us per
 // training step against 9347.
+// The 64 x 48 regions of 16th order run 256 blocks at a time (one per CU), so their
+// launches go by rounds of 256 while those of one step grow with the cells.  Over one
+// step per launch, 1 to 12 shots (forward; gradient): 256 blocks 1.37 - 1.65; 1.37 -
+// 1.57.  257 - 359 blocks 0.99 - 1.21; 0.90 - 1.05 up to 6 shots, 0.98 - 1.16 from 8
+// on.  360 - 512 blocks 1.04 - 1.28; 0.95 - 1.18.  513 - 600 blocks 0.88 - 1.05; 0.80
+// - 0.93.
 // FWI_MULTI2D=0, or FWI_DIRECT2D=0, keeps one step per launch; FWI_TB2D names a
 // shape.
-TbConfig tb_config(const Geometry &g, int njobs)
+int tb_apron(const Geometry &g, int steps);
+// (adjoint: the call has adjoint steps too)
+TbConfig tb_config(const Geometry &g, int njobs, bool adjoint)
 {
     const TbConfig none{0, 0};
     if (g.ndim != 2) return none;
@@ -401,6 +409,12 @@ TbConfig tb_config(const Geometry &g, int njobs)
     if (g.M >= 8) {
         if (cells > 300000 && (cells <= 600000 || cells > kDirect2dCells)) c = none;
         else c = TbConfig{cells <= 60000 ? 0 : cells <= 300000 ? 1 : 4, 2};
+        if (c.steps > 0 && c.shape == 1) {
+            const int A = tb_apron(g, 2);
+            const int64_t blocks = (int64_t)njobs * tb_tiles(g.nx + 2 * g.M, tb2d_width(1), A) *
+                                   tb_tiles(g.nz + 2 * g.M, tb2d_height(1), A);
+            if (blocks > 512 || (adjoint && njobs < 8 && blocks > 256 && blocks < 360)) c = none;
+        }
     } else {
         const bool wide = g.M == 4;
         c.shape = cells <= 60000 ? 0 : cells <= 300000 ? 1 : cells <= 700000 ? (wide ? 2 : 1) : 3;
