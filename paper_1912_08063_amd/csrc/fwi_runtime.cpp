@@ -1296,7 +1296,7 @@ int run_immediate(fwi_job *J, const JobOp &o)
         return FWI_OK;
     }
     case JOP_ZERO_ADJ:
-        zero(c.jobs[0].adj, 2 * fs, c.st);   // jobs step one level per launch
+        zero(c.jobs[0].adj, 2 * fs, c.st);
         zero(c.jobs[0].grad, fs, c.st);
         return FWI_OK;
     case JOP_FOLD: return fold(c, J->v, J->dv);
@@ -1438,8 +1438,9 @@ int fwi_cfl_limit(int32_t ndim, int32_t order, double *h_cfl_max)
     return FWI_OK;
 }
 
-int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *ckpt,
-                        uint64_t *h_bytes)
+// tb: whether several 2-D steps may share a launch (they need more workspace)
+static int workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *ckpt, bool tb,
+                           uint64_t *h_bytes)
 {
     if (!h_bytes) return fail(FWI_EINVAL, "NULL output");
     if (mode < FWI_MODE_FORWARD || mode > FWI_MODE_CKPT_BUF) return fail(FWI_EINVAL, "bad mode");
@@ -1448,7 +1449,7 @@ int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *c
     if (st) return st;
     Policy po;
     const int m = mode == FWI_MODE_CKPT_BUF ? FWI_MODE_FORWARD_CKPT : mode;
-    st = make_policy(prob, g, m, ckpt, &po);
+    st = make_policy(prob, g, m, ckpt, &po, tb);
     if (st) return st;
     Layout L;
     make_layout(prob, g, po, m, &L);
@@ -1456,7 +1457,12 @@ int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *c
     return FWI_OK;
 }
 
-// tb: whether several 2-D steps may share a launch (they need more workspace)
+int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *ckpt,
+                        uint64_t *h_bytes)
+{
+    return workspace_bytes(prob, mode, ckpt, true, h_bytes);
+}
+
 static int forward_call(const fwi_problem *prob, const float *v, const float *src,
                         const int32_t *src_pos, const int32_t *rec_pos, float *traces, void *ws,
                         uint64_t ws_bytes, void *stream, bool tb)
@@ -1745,8 +1751,9 @@ int fwi_job_bytes(const fwi_problem *prob, int32_t kind, int32_t chunk, const fw
     if (chunk < 1) return fail(FWI_EINVAL, "chunk must be >= 1");
     if (prob && prob->nshots != 1) return fail(FWI_EINVAL, "a job is one shot");
     const fwi_ckpt ck = job_ckpt(chunk, ckpt);
-    return fwi_workspace_bytes(prob, kind == FWI_JOB_FORWARD ? FWI_MODE_FORWARD : FWI_MODE_GRADIENT,
-                               &ck, h_bytes);
+    // (jobs step one level per launch)
+    return workspace_bytes(prob, kind == FWI_JOB_FORWARD ? FWI_MODE_FORWARD : FWI_MODE_GRADIENT,
+                           &ck, false, h_bytes);
 }
 
 int fwi_job_create(const fwi_problem *prob, int32_t kind, int32_t chunk, const fwi_ckpt *ckpt,
@@ -1767,7 +1774,7 @@ int fwi_job_create(const fwi_problem *prob, int32_t kind, int32_t chunk, const f
         const fwi_ckpt ck = job_ckpt(chunk, ckpt);
         const int mode = kind == FWI_JOB_FORWARD ? FWI_MODE_FORWARD : FWI_MODE_GRADIENT;
         Ctx &c = J->c;
-        int st = prepare(c, &J->prob, mode, &ck, mem, mem_bytes, nullptr, 0, stream);
+        int st = prepare(c, &J->prob, mode, &ck, mem, mem_bytes, nullptr, 0, stream, false);
         if (st) return st;
         const bool rec = prob->nrec > 0;
         if (!src || (rec && kind == FWI_JOB_FORWARD && !traces)) return fail(FWI_EINVAL, "NULL array");

@@ -58,3 +58,17 @@ def test_16th_order_goes_by_rounds_of_regions(nz, nx, shots, forward, gradient, 
     # the two halves of a differentiable forward agree on the checkpoint buffer
     assert _extra(p, _lib.MODE_BACKWARD, monkeypatch) == (2 if gradient else 0)
     assert _extra(p, _lib.MODE_CKPT_BUF, monkeypatch) == 0
+
+
+@pytest.mark.parametrize("nz,nx", [(64, 80), (900, 1200), (1900, 1700)])
+def test_jobs_hold_no_fields_of_multi_step_launches(nz, nx, monkeypatch):
+    """Serving jobs step one level per launch: two forward fields and two adjoint ones,
+    which is the footprint that admits them."""
+    p = _prob(nz, nx, order=8, nsponge=20)
+    got = (_lib.fwi_job_bytes(p, _lib.JOB_FORWARD, 50), _lib.fwi_job_bytes(p, _lib.JOB_GRADIENT, 50),
+           _lib.fwi_job_bytes(p, _lib.JOB_GRADIENT, 50, _lib.FwiCkpt(kind=_lib.CKPT_ALL)))
+    monkeypatch.setenv("FWI_MULTI2D", "0")
+    ck = _lib.FwiCkpt(kind=_lib.CKPT_ALL)
+    assert got == (_lib.fwi_workspace_bytes(p, _lib.MODE_FORWARD),
+                   _lib.fwi_workspace_bytes(p, _lib.MODE_GRADIENT, EVERY),
+                   _lib.fwi_workspace_bytes(p, _lib.MODE_GRADIENT, ck))
