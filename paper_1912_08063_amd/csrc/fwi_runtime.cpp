@@ -390,8 +390,8 @@ bool direct_2d(const Geometry &g, int njobs)
 // 1.57.  257 - 359 blocks 0.99 - 1.21; 0.90 - 1.05 up to 6 shots, 0.98 - 1.16 from 8
 // on.  360 - 512 blocks 1.04 - 1.28; 0.95 - 1.18.  513 - 600 blocks 0.88 - 1.05; 0.80
 // - 0.93.
-// FWI_MULTI2D=0, or FWI_DIRECT2D=0, keeps one step per launch; FWI_TB2D names a
-// shape.
+// FWI_MULTI2D=0, or FWI_DIRECT2D, which names a one-step kernel, keeps one step per
+// launch; FWI_TB2D names a shape.
 int tb_apron(const Geometry &g, int steps);
 // (adjoint: the call has adjoint steps too)
 TbConfig tb_config(const Geometry &g, int njobs, bool adjoint)
@@ -400,8 +400,7 @@ TbConfig tb_config(const Geometry &g, int njobs, bool adjoint)
     if (g.ndim != 2) return none;
     if (const char *e = getenv("FWI_MULTI2D"))
         if (atoi(e) == 0) return none;
-    if (const char *e = getenv("FWI_DIRECT2D"))
-        if (atoi(e) == 0) return none;
+    if (getenv("FWI_DIRECT2D")) return none;
     // two more fields per shot, up to 4 GiB
     if (2 * g.fstride * (int64_t)sizeof(float) * njobs > (int64_t(4) << 30)) return none;
     const int64_t cells = (int64_t)njobs * g.nz * g.nx;

@@ -72,3 +72,13 @@ def test_jobs_hold_no_fields_of_multi_step_launches(nz, nx, monkeypatch):
     assert got == (_lib.fwi_workspace_bytes(p, _lib.MODE_FORWARD),
                    _lib.fwi_workspace_bytes(p, _lib.MODE_GRADIENT, EVERY),
                    _lib.fwi_workspace_bytes(p, _lib.MODE_GRADIENT, ck))
+
+
+@pytest.mark.parametrize("direct", ["0", "1"])
+def test_naming_a_one_step_kernel_keeps_one_step_per_launch(direct, monkeypatch):
+    """FWI_DIRECT2D=0/1 forces the marching or the one-cell-per-lane kernel."""
+    p = _prob(64, 80, order=8, nsponge=10)
+    assert _extra(p, _lib.MODE_GRADIENT, monkeypatch) == 2
+    monkeypatch.setenv("FWI_DIRECT2D", direct)
+    for mode in (_lib.MODE_FORWARD, _lib.MODE_GRADIENT, _lib.MODE_BACKWARD):
+        assert _extra(p, mode, monkeypatch) == 0
