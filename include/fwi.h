@@ -81,7 +81,8 @@ enum fwi_mode {
     FWI_MODE_GRADIENT = 1,     /* fwi_gradient */
     FWI_MODE_FORWARD_CKPT = 2, /* workspace of fwi_forward_ckpt (excluding ckpt_buf) */
     FWI_MODE_BACKWARD = 3,     /* workspace of fwi_backward (excluding ckpt_buf) */
-    FWI_MODE_CKPT_BUF = 4      /* the checkpoint buffer of forward_ckpt / backward */
+    FWI_MODE_CKPT_BUF = 4,     /* the checkpoint buffer of forward_ckpt / backward */
+    FWI_MODE_ONE_STEP = 0x100  /* with a mode above: the size for one 2-D time step per launch */
 };
 
 enum fwi_ckpt_kind {
@@ -130,7 +131,12 @@ const char *fwi_last_error(void);
 int fwi_cfl_limit(int32_t ndim, int32_t order, double *h_cfl_max);
 
 /* Workspace bytes needed by an entry point (enum fwi_mode) for `prob`;
- * `ckpt` is read by the gradient modes and may be NULL otherwise.  Host-only. */
+ * `ckpt` is read by the gradient modes and may be NULL otherwise.  Host-only.
+ * 2-D calls that take several time steps per launch hold two more wavefields
+ * per shot.  Where these do not fit, mode | FWI_MODE_ONE_STEP reports the size
+ * without them, and a call whose ws_bytes is exactly that takes one time step
+ * per launch, with bitwise the same results (every other size below the full one
+ * is FWI_ENOMEM).  For other calls both sizes are the same. */
 int fwi_workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *ckpt,
                         uint64_t *h_bytes);
 

@@ -17,6 +17,7 @@ LIB_PATH = os.environ.get("FWI_LIBRARY") or os.path.join(_HERE, "libfwi.so")
 FWI_OK, FWI_EINVAL, FWI_ECFL, FWI_EBOUNDS, FWI_ENOMEM, FWI_EHIP, FWI_ENONFINITE, \
     FWI_EUNSUPPORTED = 0, -1, -2, -3, -4, -5, -6, -7
 MODE_FORWARD, MODE_GRADIENT, MODE_FORWARD_CKPT, MODE_BACKWARD, MODE_CKPT_BUF = range(5)
+MODE_ONE_STEP = 0x100   # flag: the size for one 2-D time step per launch
 CKPT_ALL, CKPT_EVERY, CKPT_REVOLVE = 0, 1, 2
 OP_ADVANCE, OP_TAKESHOT, OP_RESTORE, OP_ADJOINT, OP_RESTART = 1, 2, 3, 4, 5
 

@@ -183,6 +183,7 @@ class Workspace:
     def __init__(self, device=None):
         self.device = device
         self.buf = None
+        self.no_room = None   # a size that the device had no room for
 
     def get(self, nbytes, device):
         nbytes = max(int(nbytes), 256)
@@ -190,6 +191,25 @@ class Workspace:
             self.buf = None
             self.buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
         return self.buf
+
+
+def call_workspace(prob, mode, ck, workspace: Optional[Workspace], device):
+    """(buffer, its size for the call): the workspace of a call, or, where the device
+    has no room for it, the smaller one with which a 2-D call takes one time step per
+    launch."""
+    ws = workspace or Workspace()
+    full = _lib.fwi_workspace_bytes(prob, mode, ck)
+    if ws.no_room is None or full < ws.no_room:
+        try:
+            buf = ws.get(full, device)
+            return buf, buf.numel()
+        except torch.cuda.OutOfMemoryError:
+            if _lib.fwi_workspace_bytes(prob, mode | _lib.MODE_ONE_STEP, ck) == full:
+                raise
+            ws.no_room = full
+    small = _lib.fwi_workspace_bytes(prob, mode | _lib.MODE_ONE_STEP, ck)
+    buf = ws.get(small, device)
+    return buf, small if small < full else buf.numel()
 
 
 def forward(v, src, src_pos, rec_pos, cfg: Config, nt: Optional[int] = None,
@@ -202,8 +222,7 @@ def forward(v, src, src_pos, rec_pos, cfg: Config, nt: Optional[int] = None,
     src, src_pos, rec_pos = _shots(v, src, src_pos, rec_pos, nt)
     S, R, nt = src_pos.shape[0], rec_pos.shape[1], src.shape[1]
     prob = make_problem(v, nt, cfg, S, R)
-    nbytes = _lib.fwi_workspace_bytes(prob, _lib.MODE_FORWARD)
-    ws = (workspace or Workspace()).get(nbytes, v.device)
+    ws, ws_bytes = call_workspace(prob, _lib.MODE_FORWARD, None, workspace, v.device)
     if out is not None:
         _check_traces(out, "out", S, nt, R, v.device)
         if out.dtype != torch.float32 or not out.is_contiguous():
@@ -212,7 +231,7 @@ def forward(v, src, src_pos, rec_pos, cfg: Config, nt: Optional[int] = None,
                                                      device=v.device)
     _lib.fwi_forward(prob, v.data_ptr(), src.data_ptr(), src_pos.data_ptr(),
                      _ptr(rec_pos) if R else None, _ptr(traces) if R else None,
-                     ws.data_ptr(), ws.numel(), torch.cuda.current_stream(v.device).cuda_stream)
+                     ws.data_ptr(), ws_bytes, torch.cuda.current_stream(v.device).cuda_stream)
     return traces
 
 
@@ -229,13 +248,12 @@ def gradient(v, obs, src, src_pos, rec_pos, cfg: Config, return_traces=False,
     _check_traces(obs, "obs", S, nt, R, v.device)
     prob = make_problem(v, nt, cfg, S, R)
     ck = parse_ckpt(resolve_ckpt(cfg.ckpt, prob, v.device))
-    nbytes = _lib.fwi_workspace_bytes(prob, _lib.MODE_GRADIENT, ck)
-    ws = (workspace or Workspace()).get(nbytes, v.device)
+    ws, ws_bytes = call_workspace(prob, _lib.MODE_GRADIENT, ck, workspace, v.device)
     dv = torch.empty_like(v)
     traces = torch.empty((S, nt, R), dtype=torch.float32, device=v.device) if return_traces else None
     mis = _lib.fwi_gradient(prob, v.data_ptr(), src.data_ptr(), src_pos.data_ptr(),
                             _ptr(rec_pos) if R else None, _ptr(obs) if R else None, ck,
-                            dv.data_ptr(), _ptr(traces), ws.data_ptr(), ws.numel(),
+                            dv.data_ptr(), _ptr(traces), ws.data_ptr(), ws_bytes,
                             torch.cuda.current_stream(v.device).cuda_stream)
     if return_traces:
         return mis, dv, traces

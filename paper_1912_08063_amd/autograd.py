@@ -17,7 +17,8 @@ from __future__ import annotations
 import torch
 
 from . import _lib
-from .api import Config, _require, _shots, make_problem, parse_ckpt, resolve_ckpt
+from .api import (Config, _require, _shots, call_workspace, make_problem, parse_ckpt,
+                  resolve_ckpt)
 
 
 class FWIForward(torch.autograd.Function):
@@ -55,14 +56,13 @@ class FWIForward(torch.autograd.Function):
         grad_traces = grad_traces.to(torch.float32).contiguous()
         prob, ck = ctx.prob, ctx.ck
         stream = torch.cuda.current_stream(v.device).cuda_stream
-        ws_bytes = _lib.fwi_workspace_bytes(prob, _lib.MODE_BACKWARD, ck)
-        ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=v.device)
+        ws, ws_bytes = call_workspace(prob, _lib.MODE_BACKWARD, ck, None, v.device)
         dv = torch.empty_like(v)
         R = rec_pos.shape[1]
         _lib.fwi_backward(prob, v.data_ptr(), src.data_ptr(), src_pos.data_ptr(),
                           rec_pos.data_ptr() if R else None, ck, ctx.ckpt_buf.data_ptr(),
                           ctx.ckpt_buf.numel(), grad_traces.data_ptr() if R else None,
-                          dv.data_ptr(), ws.data_ptr(), ws.numel(), stream)
+                          dv.data_ptr(), ws.data_ptr(), ws_bytes, stream)
         # the buffers must outlive the queued kernels: hand them to the stream
         ctx.ckpt_buf.record_stream(torch.cuda.current_stream(v.device))
         ws.record_stream(torch.cuda.current_stream(v.device))

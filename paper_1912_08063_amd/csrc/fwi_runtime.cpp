@@ -91,6 +91,12 @@ static int fail(int code, const char *fmt, ...)
             return fail(FWI_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));       \
     } while (0)
 
+#define TRY(x)                   \
+    do {                         \
+        const int s_ = (x);      \
+        if (s_) return s_;       \
+    } while (0)
+
 // ---------------------------------------------------------------- geometry
 namespace {
 
@@ -599,6 +605,17 @@ int prepare(Ctx &c, const fwi_problem *p, int mode, const fwi_ckpt *ck, void *ws
     st = make_policy(p, c.g, mode, ck, &c.po, tb);
     if (st) return st;
     make_layout(p, c.g, c.po, mode, &c.L);
+    if (tb && ws_bytes < c.L.ws_total) {
+        // exactly the size without multi-step launches asks for one step per launch
+        Policy po;
+        Layout L;
+        TRY(make_policy(p, c.g, mode, ck, &po, false));
+        make_layout(p, c.g, po, mode, &L);
+        if (ws_bytes == L.ws_total) {
+            c.po = po;
+            c.L = L;
+        }
+    }
     if (!ws) return fail(FWI_EINVAL, "workspace is NULL");
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0)
         return fail(FWI_EINVAL, "workspace must be 256-byte aligned");
@@ -784,12 +801,6 @@ int stage(Ctx &c, const float *v, const float *src, const int32_t *src_pos,
     HIP_TRY(hipGetLastError());
     return FWI_OK;
 }
-
-#define TRY(x)                   \
-    do {                         \
-        const int s_ = (x);      \
-        if (s_) return s_;       \
-    } while (0)
 
 // ------------------------------------------------------------ time loops
 void plan_op(Ctx &c, int kind, int a, int b, int d, const LevelMap &lm)
@@ -1437,11 +1448,16 @@ int fwi_cfl_limit(int32_t ndim, int32_t order, double *h_cfl_max)
     return FWI_OK;
 }
 
-// tb: whether several 2-D steps may share a launch (they need more workspace)
+// tb: whether several 2-D steps may share a launch (they need more workspace; the flag
+// FWI_MODE_ONE_STEP asks for the size without)
 static int workspace_bytes(const fwi_problem *prob, int32_t mode, const fwi_ckpt *ckpt, bool tb,
                            uint64_t *h_bytes)
 {
     if (!h_bytes) return fail(FWI_EINVAL, "NULL output");
+    if (mode & FWI_MODE_ONE_STEP) {
+        mode &= ~FWI_MODE_ONE_STEP;
+        tb = false;
+    }
     if (mode < FWI_MODE_FORWARD || mode > FWI_MODE_CKPT_BUF) return fail(FWI_EINVAL, "bad mode");
     Geometry g;
     int st = make_geometry(prob, &g);

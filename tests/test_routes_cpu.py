@@ -1,9 +1,12 @@
 """Which 2-D calls take several time steps per launch, read from the workspace sizes
 (no device): such a call holds two more wavefields (adjoint calls: adjoint fields)
 per shot than FWI_MULTI2D=0, which keeps one step per launch."""
-import pytest
+import ctypes
 
-from paper_1912_08063_amd import _lib
+import pytest
+import torch
+
+from paper_1912_08063_amd import _lib, api
 
 
 def _prob(nz, nx, order=16, nsponge=0, nshots=1, nt=200, ndim=2):
@@ -82,3 +85,78 @@ def test_naming_a_one_step_kernel_keeps_one_step_per_launch(direct, monkeypatch)
     monkeypatch.setenv("FWI_DIRECT2D", direct)
     for mode in (_lib.MODE_FORWARD, _lib.MODE_GRADIENT, _lib.MODE_BACKWARD):
         assert _extra(p, mode, monkeypatch) == 0
+
+
+ALL = _lib.FwiCkpt(kind=_lib.CKPT_ALL)
+
+
+@pytest.mark.parametrize("mode,ck,fields", [
+    (_lib.MODE_FORWARD, None, 2), (_lib.MODE_GRADIENT, EVERY, 2), (_lib.MODE_GRADIENT, ALL, 2),
+    (_lib.MODE_BACKWARD, EVERY, 2), (_lib.MODE_FORWARD_CKPT, EVERY, 0), (_lib.MODE_CKPT_BUF, EVERY, 0),
+    (_lib.MODE_GRADIENT, _lib.FwiCkpt(kind=_lib.CKPT_REVOLVE, slots=3), 0)])
+def test_one_step_size(mode, ck, fields, monkeypatch):
+    """The flag MODE_ONE_STEP reports what FWI_MULTI2D=0 reports: the fields of
+    multi-step launches less."""
+    p = _prob(64, 80, order=8, nsponge=10, nshots=3)
+    small = _lib.fwi_workspace_bytes(p, mode | _lib.MODE_ONE_STEP, ck)
+    assert _lib.fwi_workspace_bytes(p, mode, ck) - small == fields * 3 * _field(p)
+    monkeypatch.setenv("FWI_MULTI2D", "0")
+    assert _lib.fwi_workspace_bytes(p, mode, ck) == small
+
+
+def test_unknown_modes_stay_refused():
+    p = _prob(64, 80)
+    for mode in (-1, 5, 0x200, _lib.MODE_ONE_STEP | 5, 0x201):
+        with pytest.raises(_lib.FwiError) as e:
+            _lib.fwi_workspace_bytes(p, mode, EVERY)
+        assert e.value.status == _lib.FWI_EINVAL
+
+
+def test_a_workspace_of_exactly_the_one_step_size_is_accepted():
+    """It passes the size check (and is refused for its NULL arrays); a byte less or
+    more is FWI_ENOMEM, as every size below the full one was."""
+    p = _prob(64, 80, order=8, nsponge=10)
+    lib = _lib.load()
+    small = _lib.fwi_workspace_bytes(p, _lib.MODE_FORWARD | _lib.MODE_ONE_STEP)
+    full = _lib.fwi_workspace_bytes(p, _lib.MODE_FORWARD)
+
+    def call(n):
+        return lib.fwi_forward(ctypes.byref(p), None, None, None, None, None, 256, n, None)
+
+    assert call(small) == call(full) == _lib.FWI_EINVAL
+    for n in (0, small - 1, small + 1, small + 256, full - 1):
+        assert call(n) == _lib.FWI_ENOMEM
+
+
+class _Device:
+    """Stands in for a device's memory: refuses allocations above `room` bytes."""
+
+    def __init__(self, room):
+        self.room, self.asked = room, []
+
+    def empty(self, n, dtype=None, device=None):
+        self.asked.append(n)
+        if n > self.room:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return torch.zeros(n, dtype=dtype)
+
+
+def test_a_device_without_room_takes_the_smaller_workspace(monkeypatch):
+    p = _prob(64, 80, order=8, nsponge=10)
+    size = lambda flag: _lib.fwi_workspace_bytes(p, _lib.MODE_GRADIENT | flag, EVERY)
+    full, small = size(0), size(_lib.MODE_ONE_STEP)
+    cpu = torch.device("cpu")
+    get = lambda ws: api.call_workspace(p, _lib.MODE_GRADIENT, EVERY, ws, cpu)
+    dev = _Device(full - 1)
+    monkeypatch.setattr(api.torch, "empty", dev.empty)
+    ws = api.Workspace()
+    for _ in range(2):   # and is not asked for the larger one at every call
+        buf, n = get(ws)
+        assert n == small and buf.numel() == small
+    assert dev.asked == [full, small]
+    dev.room = full
+    buf, n = get(api.Workspace())
+    assert n == full and buf.numel() == full
+    dev.room = small - 1
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        get(api.Workspace())
