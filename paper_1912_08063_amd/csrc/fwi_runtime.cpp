@@ -1906,9 +1906,9 @@ int run_ops(fwi_job *J, const std::vector<JobOp> &ops)
 // the order of its own stream.  (Behind it on the GPU: the host waits for nothing.)
 // Sets of side streams come from a pool of at most kSets per device, shared by all
 // threads; a set goes back when its call has enqueued its work, and serves any
-// caller next, in stream order.  Without a free set, or while the caller's stream
-// is captured into a graph, everything goes to the caller's stream, as with
-// FWI_LANES=1.
+// caller next, in stream order.  Without a free set, while the caller's stream is
+// captured into a graph, or if it belongs to another device than the current one,
+// everything goes to the caller's stream, as with FWI_LANES=1.
 class Lanes {
 public:
     static constexpr int kSide = 3, kSets = 8;
@@ -1920,7 +1920,7 @@ public:
         if (want < 2) return;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
-            !(set_ = take(st))) {
+            !on_current_device(st) || !(set_ = take(st))) {
             (void)hipGetLastError();
             return;
         }
@@ -1973,6 +1973,15 @@ private:
         std::mutex m;
         std::vector<Set *> sets;
     };
+    // Launches go to their stream's device, new streams to the current one.
+    static bool on_current_device(hipStream_t st)
+    {
+        if (!st || st == hipStreamPerThread) return true;
+        int current = 0;
+        hipDevice_t own = -1;
+        return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(st, &own) == hipSuccess &&
+               own == current;
+    }
     // (never destroyed: the HIP runtime may be gone by then)
     static Pool &pool()
     {

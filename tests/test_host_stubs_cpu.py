@@ -1,0 +1,43 @@
+"""The library's host code over a HIP runtime that only takes notes
+(host_stubs.cpp): the streams it uses and the order of its launches and waits, which
+one GPU cannot show."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1912_08063_amd", "csrc")
+
+
+def _build(out, flags=()):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ is not available")
+    subprocess.run([gxx, "-O1", "-g", "-std=c++17", *flags, "-D__HIP_PLATFORM_AMD__",
+                    "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "host_stubs.cpp"),
+                    os.path.join(CSRC, "fwi_runtime.cpp"), os.path.join(CSRC, "revolve.cpp"),
+                    "-pthread", "-o", out], check=True)
+    return out
+
+
+@pytest.fixture(scope="module")
+def stubs(tmp_path_factory):
+    return _build(str(tmp_path_factory.mktemp("stubs") / "stubs"))
+
+
+def _run(exe, *args):
+    p = subprocess.run([exe, *args], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout + p.stderr
+    return p.stdout.split("\n")[:-1]
+
+
+def test_side_streams_only_on_the_callers_device(stubs):
+    """Launch groups of one advance go to side streams, but not where the caller's
+    stream belongs to another device than the current one: side streams are of the
+    current device."""
+    steps, streams = _run(stubs, "lanes", "0")[0].split()[1:4:2]
+    assert int(steps) == 8 and int(streams) == 2
+    assert _run(stubs, "lanes", "1") == ["steps 8 streams 1 caller 1"]
