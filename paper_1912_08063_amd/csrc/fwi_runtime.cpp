@@ -1807,14 +1807,13 @@ int fwi_job_create(const fwi_problem *prob, int32_t kind, int32_t chunk, const f
         st = stage(c, v, src, src_pos, rec_pos, rec ? J->rec : nullptr, J->res,
                    kind == FWI_JOB_GRADIENT);
         if (st) return st;
-        // the job may be advanced on another stream, and its inputs released
-        HIP_TRY(hipStreamSynchronize(c.st));
-        // frames of every level; levels 0 and -1 whole (the job's program
-        // also clears them before its first step)
+        // frames of every level; levels 0 and -1 whole
         zero_frames(c, c.jobs[0].ring, (uint64_t)c.po.R);
         zero(c.jobs[0].ring, (uint64_t)c.g.fstride, c.st);
         zero(c.jobs[0].ring + (uint64_t)c.g.fstride * (c.po.R - 1), (uint64_t)c.g.fstride, c.st);
         HIP_TRY(hipGetLastError());
+        // the job may be advanced on another stream, and its positions released
+        HIP_TRY(hipStreamSynchronize(c.st));
         J->rounds = kind == FWI_JOB_GRADIENT && c.po.kind == FWI_CKPT_REVOLVE;
         build_program(J.get());
         *h_job = J.release();

@@ -41,3 +41,11 @@ def test_side_streams_only_on_the_callers_device(stubs):
     steps, streams = _run(stubs, "lanes", "0")[0].split()[1:4:2]
     assert int(steps) == 8 and int(streams) == 2
     assert _run(stubs, "lanes", "1") == ["steps 8 streams 1 caller 1"]
+
+
+def test_a_created_job_has_nothing_in_flight(stubs):
+    """fwi_job_create synchronises its stream after all it enqueues: the job may be
+    advanced on another stream, whose first step reads the cleared levels."""
+    did = _run(stubs, "create")
+    assert did[0] == "check" and {"tables", "kappa", "frames", "fill"} <= set(did)
+    assert did[-1] == "sync"
