@@ -475,6 +475,22 @@ int step_code(const Geometry &g, int njobs, bool adj)
     return (int64_t)njobs * g.nz * g.ny * g.nx <= most ? kTile3dCode : kMarch3dCode;
 }
 
+// Compute units of the device that is current at the first call (256 without one).
+int compute_units()
+{
+    static std::atomic<int> known{0};
+    int n = known.load(std::memory_order_relaxed);
+    if (n == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+            n = prop.multiProcessorCount;
+        if (n <= 0) n = 256;
+        known.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 void tiles_for(const Geometry &g, int njobs, int code, int *ntx, int *nty, int *nzc, int *zc)
 {
     const int M = g.M;
@@ -498,14 +514,7 @@ void tiles_for(const Geometry &g, int njobs, int code, int *ntx, int *nty, int *
         // 560 x 560 x 304, forward and adjoint: 76 planes 885 (420), 51 904
         // (472), 38 910 (501), 102 949 (539), 61 956 (545); 240^3: 30 43.0 (76), 60
         // 46.1 (129).  Chunks are at least 4 planes.
-        static int cus = 0;
-        if (cus == 0) {
-            int dev = 0;
-            hipDeviceProp_t prop;
-            if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-                cus = prop.multiProcessorCount;
-            if (cus <= 0) cus = 256;
-        }
+        const int cus = compute_units();
         double best = 0.0;
         z = g.nz;
         for (int n = 1; n <= std::max(1, g.nz / 4); ++n) {
