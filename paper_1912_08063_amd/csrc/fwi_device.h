@@ -129,12 +129,6 @@ __device__ __forceinline__ float leapfrog(float val, float prev, int d2, float e
            fmaf(-fmaf(-eta_dt, (float)d2, 1.f), prev, val);
 }
 
-// Streams read or written once per launch (kappa', the previous level, the
-// new level, the gradient accumulator) are non-temporal, leaving L2 to the
-// rows that neighbouring tiles share (+4 % on the 3-D forward step; keeping
-// kappa' or the new level cached instead, for reuse by the next step from the
-// Infinity Cache, measured no faster).  FWI_STREAM_CACHED at build time
-// restores ordinary accesses.
 // Field pointers come from the job table, so the compiler cannot see that
 // they address global memory; without the cast every access would be a
 // flat load (64-bit address arithmetic per access, and flat loads also hold
@@ -151,6 +145,17 @@ __device__ __forceinline__ gfloat *gptr(float *p) { return (gfloat *)p; }
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit buffer, CDNA
 constexpr int kCacheNT = 2;              // non-temporal cache policy
+// Streams read or written once per launch (kappa', the previous level, the
+// new level, the gradient accumulator) are non-temporal, leaving L2 to the
+// rows that neighbouring tiles share (+4 % on the 3-D forward step; keeping
+// kappa' or the new level cached instead, for reuse by the next step from the
+// Infinity Cache, measured no faster).  FWI_STREAM_CACHED at build time
+// restores ordinary accesses.
+#ifdef FWI_STREAM_CACHED
+constexpr int kStreamPolicy = 0;
+#else
+constexpr int kStreamPolicy = kCacheNT;
+#endif
 
 __device__ __forceinline__ rsrc_t plane_rsrc(const gfloat *f, int zmem, int64_t plane,
                                              int pbytes)
@@ -164,21 +169,13 @@ __device__ __forceinline__ float ldb(rsrc_t r, uint32_t boff)
 }
 __device__ __forceinline__ float ldb_stream(rsrc_t r, uint32_t boff)
 {
-#ifdef FWI_STREAM_CACHED
-    return ldb(r, boff);
-#else
     return __builtin_bit_cast(float,
-                              __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, kCacheNT));
-#endif
+                              __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, kStreamPolicy));
 }
 __device__ __forceinline__ void stb_stream(rsrc_t r, uint32_t boff, float v)
 {
-#ifdef FWI_STREAM_CACHED
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)boff, 0, 0);
-#else
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)boff, 0,
-                                          kCacheNT);
-#endif
+                                          kStreamPolicy);
 }
 
 // Plane of a field: element (z, row, col) is at base[(z + M) * plane + row_offset].

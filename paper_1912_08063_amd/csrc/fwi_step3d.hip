@@ -23,11 +23,13 @@ __device__ __forceinline__ vf4 ldb4(rsrc_t r, uint32_t off)
 }
 __device__ __forceinline__ vf4 ldb4_stream(rsrc_t r, uint32_t off)
 {
-    return __builtin_bit_cast(vf4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kCacheNT));
+    return __builtin_bit_cast(vf4,
+                              __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kStreamPolicy));
 }
 __device__ __forceinline__ void stb4_stream(rsrc_t r, uint32_t off, vf4 v)
 {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4, v), r, (int)off, 0, kCacheNT);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4, v), r, (int)off, 0,
+                                           kStreamPolicy);
 }
 
 // Stencil sums of a thread's four columns: L is its place in the staged plane
