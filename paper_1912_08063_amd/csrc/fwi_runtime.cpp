@@ -439,9 +439,11 @@ TbConfig tb_config(const Geometry &g, int njobs, bool adjoint)
 // Apron of a launch of up to `steps` steps: whole patches (4 columns, rows)
 int tb_apron(const Geometry &g, int steps) { return (steps * g.M + 3) / 4 * 4; }
 
-// Rows per chunk of two-step marching forward launches (0: k_step2d_tb): from
-// 2.5 M cells (8 shots of 1064 x 360: 3129 against 3203 us per 300 steps; 16:
-// 4666 against 5755; 4: 2231 against 1909), the longest chunks of up to 48 rows
+// Rows per chunk of two-step marching forward launches (0: k_step2d_tb): at 8th order
+// from 2.5 M cells (8 shots of 1064 x 360: 3129 against 3203 us per 300 steps; 16:
+// 4666 against 5755; 4: 2231 against 1909), at 4th order, where the apron of
+// k_step2d_tb is half as wide, from 10 M (us per 100 steps, 8 shots 907 against 800,
+// 16 1301 against 1215, 32 2036 against 2148); the longest chunks of up to 48 rows
 // that give 2048 waves (32 shots: 48 rows 14.3 ms, 36 16.6, 24 15.2; 16 shots:
 // 24 rows 4666 us, 48 5587, 12 5018).  Fields are addressed by 32-bit offsets.
 // FWI_PIPE2D sets the rows (0: off).
@@ -450,7 +452,7 @@ int pipe_rows(const Geometry &g, int njobs, int ntx)
     if ((g.M != 2 && g.M != 4) || g.fstride * (int64_t)sizeof(float) >= kPipeFieldBytes) return 0;
     const int u = pipe2d_group(g.M);
     if (const char *e = getenv("FWI_PIPE2D")) return std::max(0, (atoi(e) + u - 1) / u * u);
-    if ((int64_t)njobs * g.nz * g.nx < 2500000) return 0;
+    if ((int64_t)njobs * g.nz * g.nx < (g.M == 2 ? 10000000 : 2500000)) return 0;
     int zc = 48 / u * u;
     while (zc > u && (int64_t)ntx * njobs * ((g.nz + zc - 1) / zc) < 2048) zc -= u;
     return zc;
@@ -461,9 +463,11 @@ int pipe_rows(const Geometry &g, int njobs, int ntx)
 // order forward: 80^3 padded cells 6.3 (7.1), 112^3 8.2 (8.1), 144^3 14.7 (15.4),
 // 176^3 19.8 (20.0), 208^3 31.8 (35.8), 256^3 57 (55); gradient, every step
 // recomputed once: 80^3 20.5 (25.1), 144^3 58.8 (62.2), 208^3 136 (142), 232^3 177
-// (170), 256^3 288 (232).  At 16th order the halo is twice as wide: 64^3 6.5 (9.4),
-// 80^3 8.1 (9.7), 88^3 11.4 (10.9), 112^3 12.7 (11.4).  FWI_TILE3D sets the largest
-// number of cells.
+// (170), 256^3 288 (232).  Orders 4 and 2, per 100 forward steps: 104^3 760 (837) and
+// 734 (838), 176^3 1905 (2033) and 1879 (1915), 208^3 3152 (3453) and 3124 (3404),
+// 256^3 5629 (5497) and 6035 (5481); gradients as at 8th order.  At 16th order the
+// halo is twice as wide: 64^3 6.5 (9.4), 80^3 8.1 (9.7), 88^3 11.4 (10.9), 112^3 12.7
+// (11.4).  FWI_TILE3D sets the largest number of cells.
 int64_t tile3d_cells(int M) { return M >= 8 ? 600000 : 10000000; }
 int step_code(const Geometry &g, int njobs, bool adj)
 {

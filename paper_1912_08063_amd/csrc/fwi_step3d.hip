@@ -377,7 +377,7 @@ __global__ __launch_bounds__(256) void k_step3d(const Job *__restrict__ jobs,
 // neighbouring blocks share are read at the same time on one XCD.  Two planes a
 // block: a launch is bound by its latency, and more, smaller blocks hide it better
 // than fewer reads of the shared planes (112^3 padded cells, 8th order, us per
-// step: 1 plane 10.6, 2 planes 10.1, 3 10.7, 4 10.9, 6 13.5, 8 14.2).  The
+// step: 1 plane 9.5, 2 planes 8.4, 3 8.9, 4 9.0, 6 11.2).  The
 // arithmetic is k_step3d's, term by term.  The adjoint is fused and adds the
 // adjoint source itself, from the receivers of each 64 x TY x 1 slice.
 template <int M, bool ADJ>

@@ -116,17 +116,27 @@ void launch_fold(int, const Job *, int, int, int, int, int, int, int, int, int, 
 int vstats_blocks() { return 1; }
 int range_blocks() { return 1; }
 void launch_vstats(const float *, int64_t, float *, int, hipStream_t st) { note("stats", st); }
-void launch_nonfinite_level(const Job *, int, int, float *, hipStream_t st) { note("level", st); }
+void launch_nonfinite_level(const Job *, int, int, float *partial, hipStream_t st)
+{
+    partial[0] = 0.f;
+    note("level", st);
+}
 void launch_assemble(const AssembleArgs &, Job *, int *, int32_t *, hipStream_t st)
 {
     note("assemble", st);
 }
 int tb2d_width(int) { return 64; }
 int tb2d_height(int) { return 64; }
-void launch_step2d_tb(int, int, bool, const Job *, int, const TbLaunch &, hipStream_t) {}
+void launch_step2d_tb(int, int, bool, const Job *, int, const TbLaunch &, hipStream_t st)
+{
+    note("tile steps", st);
+}
 int pipe2d_width() { return 128; }
 int pipe2d_group(int) { return 12; }
-void launch_step2d_pipe(int, const Job *, int, const PipeLaunch &, hipStream_t) {}
+void launch_step2d_pipe(int, const Job *, int, const PipeLaunch &, hipStream_t st)
+{
+    note("marching steps", st);
+}
 void launch_gather2(const Job *, int, int, int, int, int, hipStream_t) {}
 void launch_trace_duplicates(const Job *, int, int, int, hipStream_t) {}
 int scratch_address(void **p) { *p = nullptr; return -1; }
@@ -203,6 +213,29 @@ void lanes(int device)
     printf("steps %d streams %zu caller %d\n", steps, used.size(), (int)used.count(st));
 }
 
+// The kinds of step launches of a 2-D forward of `shots` shots of 1024 x 320 cells.
+void forward(int order, int shots)
+{
+    fwi_problem p = problem(order);
+    p.shape[0] = 320;
+    p.shape[1] = 1024;
+    p.nsponge = 20;
+    p.nshots = shots;
+    p.nrec = 0;
+    static float data[1 << 20];
+    static int32_t pos[1 << 10];
+    uint64_t n = 0;
+    if (fwi_workspace_bytes(&p, FWI_MODE_FORWARD, nullptr, &n) != FWI_OK ||
+        fwi_forward(&p, data, data, pos, nullptr, nullptr, memory(n), n, nullptr) != FWI_OK) {
+        printf("failed: %s\n", fwi_last_error());
+        exit(2);
+    }
+    std::set<std::string> kinds;
+    for (const Note &x : g_notes)
+        if (x.what.find("step") != std::string::npos) kinds.insert(x.what);
+    for (const std::string &k : kinds) printf("%s\n", k.c_str());
+}
+
 // Two threads that both need the device's number of compute units first.
 void threads()
 {
@@ -224,6 +257,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "create") create();
     else if (what == "lanes") lanes(argc > 2 ? atoi(argv[2]) : 0);
+    else if (what == "forward") forward(argc > 2 ? atoi(argv[2]) : 8, argc > 3 ? atoi(argv[3]) : 1);
     else if (what == "threads") threads();
     else return 3;
     return 0;

@@ -49,3 +49,12 @@ def test_a_created_job_has_nothing_in_flight(stubs):
     did = _run(stubs, "create")
     assert did[0] == "check" and {"tables", "kappa", "frames", "fill"} <= set(did)
     assert did[-1] == "sync"
+
+
+@pytest.mark.parametrize("order,shots,kind", [
+    (4, 1, "tile"), (4, 6, "tile"), (4, 8, "tile"), (4, 16, "tile"), (4, 32, "marching"),
+    (8, 1, "tile"), (8, 6, "tile"), (8, 8, "marching"), (8, 32, "marching")])
+def test_two_step_marching_by_cells_and_order(order, shots, kind, stubs):
+    """Forward launches of 2.5 M cells and more march two steps at 8th order, of 10 M
+    and more at 4th order."""
+    assert _run(stubs, "forward", str(order), str(shots)) == [kind + " steps"]
