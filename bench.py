@@ -93,13 +93,15 @@ def median_time(fn, reps, sync):
 
 
 def tile_march(dev, P, step_us, reps=50):
-    """The forward step's memory pattern without its stencil (fwi_tile_probe):
-    the same 64 x 16 tiles, z-chunks (the step's own choice for this grid),
-    block order and buffer loads, writing 2 cur + kappa prv.  Timed with HIP
+    """The memory pattern of a marching step with one column per lane, without a
+    stencil (fwi_tile_probe): the forward step's 64 x 16 tiles, z-chunks and block
+    order, but 4-byte accesses where the step has 16-byte ones, writing 2 cur +
+    kappa prv.  Timed with HIP
     events bare, with the halo loads, with the LDS staging and barrier, and
-    with the z-chunk warm-up planes as well (the step's whole access pattern),
+    with the z-chunk warm-up planes as well (the whole pattern),
     and the bare march and its halo loads with 64-bit loads per lane;
-    `step_frac_of_pattern` is the whole pattern's time over the step's."""
+    `step_frac_of_pattern` is the whole pattern's time over the step's: above 1
+    by what the step's wider accesses gain."""
     import torch
     from paper_1912_08063_amd import _lib
     st = torch.cuda.current_stream(dev)
@@ -605,7 +607,7 @@ def main():
     ap.add_argument("--sections",
                     default="forward,ceiling,c1,forward16,slab,gradient,gradient3d,salt3d,serve",
                     help="comma list of: forward (headline), ceiling (3-read/1-write stream "
-                         "probe and the step's tile-march pattern), c1 (2-D one-shot latency), forward16 (16th order), slab (one "
+                         "probe and a tile-march pattern), c1 (2-D one-shot latency), forward16 (16th order), slab (one "
                          "GPU's z-slab of a 1024^3 model), gradient (2-D, 32 shots), "
                          "gradient3d (headline geometry), salt3d (salt model, revolve), serve "
                          "(request streams)")

@@ -33,12 +33,12 @@
  *     damping held fixed.  Outputs are overwritten, never accumulated.
  *   - Work is enqueued on `stream` (a hipStream_t, NULL = default stream);
  *     results are valid once the stream is synchronised.  A propagating call
- *     first copies the (small) position arrays to the host and measures the
- *     velocity range with one reduction kernel into the workspace, then
- *     synchronises `stream` to validate them; fwi_forward, fwi_forward_ckpt,
- *     fwi_backward and fwi_gradient also synchronise it at the end, for the
- *     non-finite check below.  The time loop itself runs without host
- *     synchronisation.
+ *     first checks the positions, measures the velocity range and builds its
+ *     tables on the device, then synchronises `stream` to read the verdict
+ *     (and twice more where receivers share a cell); fwi_forward,
+ *     fwi_forward_ckpt, fwi_backward and fwi_gradient also synchronise it at
+ *     the end, for the non-finite check below.  The time loop itself runs
+ *     without host synchronisation.
  *   - Workspaces: the caller allocates `ws` (>= the size reported by
  *     fwi_workspace_bytes, 256-byte aligned) and keeps it alive until the
  *     stream has finished the call's work.  The library allocates no device
@@ -48,8 +48,8 @@
  * Errors: every entry point returns an int status (FWI_OK == 0, negative on
  * error).  Shapes, sizes and pointers are checked on the host before any
  * kernel is launched; positions, velocities and the stability limit right
- * after the velocity-range kernel (which writes only the workspace) and
- * before any step.  On those errors no output is written.  FWI_ENONFINITE is
+ * after the staging kernels (which write only the workspace of a call that is
+ * refused) and before any step.  On those errors no output is written.  FWI_ENONFINITE is
  * the exception: it is detected after the outputs were written (a non-finite
  * last wavefield, misfit or gradient), and the outputs then hold whatever the
  * run produced.  Asynchronous device faults surface as FWI_EHIP on a later
@@ -162,9 +162,11 @@ int fwi_forward(const fwi_problem *prob, const float *v, const float *src,
  * passes only inputs and outputs.  Calls no hipMalloc or hipFree.  The
  * array is shared by every call on the same GPU: calls that overlap on one
  * GPU (other streams, other host threads) race; serialise them.  Each call
- * initialises every part of the array it reads.  FWI_ENOMEM if the problem
- * needs more workspace than the array holds (fwi_workspace_bytes, mode
- * FWI_MODE_FORWARD); otherwise the errors of fwi_forward.
+ * initialises every part of the array it reads.  A 2-D problem that fits the
+ * array only with one time step per launch takes one.  FWI_ENOMEM if the problem
+ * needs more workspace than the array holds even so (fwi_workspace_bytes, mode
+ * FWI_MODE_FORWARD | FWI_MODE_ONE_STEP; 1 MiB beside the array holds the staging
+ * records); otherwise the errors of fwi_forward.
  */
 int fwi_forward_noalloc(const fwi_problem *prob, const float *v, const float *src,
                         const int32_t *src_pos, const int32_t *rec_pos, float *traces,
@@ -230,22 +232,24 @@ int fwi_stream_probe(const float *a, const float *b, const float *c, float *out,
                      int32_t variant, void *stream);
 
 /*
- * Diagnostic: the 8th-order forward step's memory pattern with the stencil
- * taken out, to separate what the pattern costs from what the stencil
- * costs.  Not part of the method.  The four device fields are laid out as
+ * Diagnostic: the memory pattern of an 8th-order 3-D step that marches with
+ * one column per lane (4-byte accesses), with the stencil taken out.  The
+ * present forward step marches the same tiles with four columns per lane, so
+ * the probe is a yardstick for it, not its own pattern.  Not part of the
+ * method.  The four device fields are laid out as
  * the 3-D step's (each nz + 8 planes of ny + 8 rows of pitch floats, pitch =
  * nx + 8 rounded up to a multiple of 64, the 4-cell frame included; fields
  * 16-byte aligned).  Blocks of 4 wavefronts march 64 x 16 column tiles
  * through z chunks of zc planes in the step's block order, read cur, prv and
  * kap once per cell one plane ahead and write out = 2 cur + kap * prv at
  * the nz x ny x nx cells inside the frame; nothing else is written.  Mode
- * bits add the step's other work one at a time: 1 the tile's halo rows and
+ * bits add such a step's other work one at a time: 1 the tile's halo rows and
  * columns of cur, 2 the plane staged in LDS with one barrier per plane, 4
- * the 4 + 4 planes of cur around each chunk that the step's z-queue reads;
+ * the 4 + 4 planes of cur around each chunk that a z-queue reads;
  * modes 8 and 9 are modes 0 and 1 with 64-bit loads and stores (each lane
  * two adjacent columns).  The output is the same in every mode for finite
  * inputs.  zc = 0 takes
- * the chunk length the forward step picks for this grid; *h_zc (may be
+ * the chunk length of the marching forward step on this grid; *h_zc (may be
  * NULL) receives the length used.  Asynchronous on `stream`.  FWI_EINVAL on
  * a bad argument (NULL field, out equal to an input, a grid dimension out
  * of 1 .. 2^20, a plane of 2^31 bytes or more, zc < 0, mode outside 0..9).

@@ -178,18 +178,6 @@ __device__ __forceinline__ void stb_stream(rsrc_t r, uint32_t boff, float v)
                                           kStreamPolicy);
 }
 
-// Plane of a field: element (z, row, col) is at base[(z + M) * plane + row_offset].
-// The plane base is uniform across the block (scalar registers); per-thread
-// offsets within a plane are 32-bit, so every load is base + 32-bit offset.
-__device__ __forceinline__ const gfloat *plane_ptr(const gfloat *f, int zmem, int64_t plane)
-{
-    return f + (int64_t)zmem * plane;
-}
-__device__ __forceinline__ gfloat *plane_ptr(gfloat *f, int zmem, int64_t plane)
-{
-    return f + (int64_t)zmem * plane;
-}
-
 // Compile-time loop: f(Int<I>{}) for I = B .. E-1, fully unrolled, so an
 // index derived from I can select a register.
 template <int V>

@@ -18,7 +18,7 @@
 //    chunk of z planes.  Each thread keeps a register queue of 2M+2 planes of
 //    four columns for the z-derivative (z marching), and the current xy plane
 //    with its M-cell halo is staged in LDS for the x and y derivatives.  Small
-//    grids take blocks of 64 x 16 x 4 cells instead (fwi_step3d.hip).
+//    grids take blocks of 64 x 16 x 2 cells instead (fwi_step3d.hip).
 //  * 2-D: one wavefront per block, 64 columns marching down a chunk of rows;
 //    runs of consecutive steps take several steps per launch (fwi_step2d.hip).
 //  * Wavefronts read and write whole aligned 256-byte row segments.
@@ -671,14 +671,15 @@ void launch_stream_probe(const float *a, const float *b, const float *c, float *
 }
 
 // ------------------------------------------------ tile-march pattern probe
-// The 8th-order forward step's memory pattern with the stencil taken out:
+// The memory pattern of an 8th-order marching step with one column per lane
+// (k_step3d has four, in 16-byte accesses), with the stencil taken out:
 // blocks of 4 wavefronts x 4 rows march 64 x 16 column tiles through z
 // chunks in the step's block order (XCD-remapped), load cur, prv and kappa
 // once per cell through buffer resources (prv and kappa non-temporal) one
-// plane ahead, and write out = 2 cur + kappa prv with the step's store.
-// Mode bits add the step's other traffic and synchronisation one at a
-// time: 1 the halo rows and columns of cur (loaded one plane ahead, as the
-// step's 16th-order kernels and adjoints do), 2 the plane staged in LDS
+// plane ahead, and write out = 2 cur + kappa prv.
+// Mode bits add such a step's other traffic and synchronisation one at a
+// time: 1 the halo rows and columns of cur (loaded one plane ahead),
+// 2 the plane staged in LDS
 // behind the LDS-only barrier (the written cur value then comes from LDS),
 // 4 the 2M warm-up planes of cur each chunk reads around its own.  Halo and
 // warm-up values enter only a sum scaled by `zero` (0 from the host), so

@@ -2110,7 +2110,7 @@ int fwi_jobs_advance(fwi_job *const *jobs, int32_t njobs, int32_t ksteps, void *
             }
             g.table.push_back(x);
             g.tp.push_back(g.tp.back() + t.tile[isadj ? 1 : 0].ntiles);
-            g.gp.push_back(g.gp.back() + ((!isadj && record) || isadj ? t.ngather : 0));
+            g.gp.push_back(g.gp.back() + (!isadj && record ? t.ngather : 0));
         };
         std::vector<RoundPlan> plans(njobs);
         for (int i = 0; i < njobs; ++i) {

@@ -47,8 +47,10 @@ def test_equal_to_the_one_cell_per_lane_kernel(order, monkeypatch):
     assert np.array_equal(got[1], ref[1]) and np.array_equal(got[2], ref[2])
 
 
-@pytest.mark.parametrize("ckpt", ["all", "every:7"])
-def test_results_do_not_depend_on_workspace_contents(ckpt, monkeypatch):
+@pytest.mark.parametrize("pipe", ["0", "12"])   # tiled; two-step marching forward launches
+@pytest.mark.parametrize("ckpt", ["all", "every:7", "every:12"])
+def test_results_do_not_depend_on_workspace_contents(ckpt, pipe, monkeypatch):
+    monkeypatch.setenv("FWI_PIPE2D", pipe)
     P = f32(wl.small_2d(nz=48, nx=131, nt=90, order=8, nshots=2, nrec=40))
     assert _multi(P, ckpt, monkeypatch)
     obs = np.asarray(oracle_forward(P), dtype=np.float32).astype(np.float64)
